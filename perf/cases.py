@@ -8,8 +8,7 @@ contiguous chunks, and how many contexts of how many tokens one pass moves:
   swap      offload of one set of contexts, then load of another set into
             other pages, in turn on one stream (an eviction followed by a hit)
   both_ways the same two transfers at once on two streams: the load with the
-            library's defaults on a stream with a queue of its own, the offload
-            with the background quota (16 workgroups of one wave, 4 KiB steps)
+            library's defaults, the offload with the background quota (16 workgroups of one wave, 4 KiB steps)
   layers    one call and one event per layer on a transfer stream; the
             compute stream waits for every layer's event
   noalloc   the load that takes a pool description instead of a handle
@@ -152,15 +151,14 @@ class _State:
     pass
 
 
-_transfer_stream = None
+_streams = {}
 
 
-def _stream():
-    """The program's transfer stream, with a hardware queue of its own."""
-    global _transfer_stream
-    if _transfer_stream is None:
-        _transfer_stream = kv.Stream(list(range(torch.cuda.get_device_properties(0).multi_processor_count)))
-    return _transfer_stream.torch
+def _stream(role):
+    """The program's stream for this role, made once: a few streams, each with a hardware queue to itself."""
+    if role not in _streams:
+        _streams[role] = kv.Stream()
+    return _streams[role].torch
 
 
 def prepare(case, seed):
@@ -198,10 +196,9 @@ def prepare(case, seed):
     s.handle = kv.KVPool(s.pool, P, load_launch=mode, offload_launch=back, host_layout=layout)
     if case["op"] == "layers":
         s.events = [torch.cuda.Event() for _ in range(L)]
-    if case["op"] in ("layers", "both_ways"):
-        s.io = _stream()
+        s.io = _stream("transfer")
     if case["op"] == "both_ways":
-        s.background = torch.cuda.Stream()
+        s.io, s.background = _stream("transfer"), _stream("background")
     return s
 
 
