@@ -52,13 +52,6 @@ using kvio::Resolved;
 
 namespace {
 
-int ilog2_exact(int64_t v) {
-    if (v <= 0 || (v & (v - 1)) != 0) return -1;
-    int s = 0;
-    while ((int64_t(1) << s) < v) ++s;
-    return s;
-}
-
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 constexpr int64_t kDefaultStagingBytes = int64_t(4) << 30;
@@ -78,7 +71,8 @@ Shape resolve(const kvio_launch &l, const Shape &def) {
     s.threads = l.threads > 0 ? l.threads : def.threads;
     s.tile_kib = l.tile_kib > 0 ? l.tile_kib : def.tile_kib;
     s.nontemporal = (l.flags & KVIO_LAUNCH_CACHED) == 0;
-    s.head_major_lds = (l.flags & KVIO_LAUNCH_NO_LDS) == 0;
+    s.grows = l.workgroups == 0;
+    s.device_scope = s.nontemporal && int64_t(s.workgroups) * (s.threads / 64) * s.tile_kib * 1024 >= kSc1MinInflight;
     return s;
 }
 
@@ -389,72 +383,126 @@ kvio_status validate_spans(const PoolGeom &g, const kvio_span *spans, int32_t n,
 
 // Fields of a launch that do not depend on its spans.
 void common_args(const PoolGeom &g, uint8_t *const *layers, unsigned long long *err, const Shape &shape,
-                 int32_t l0, CopyArgs *a) {
+                 Direction dir, int32_t l0, CopyArgs *a) {
     memset(a, 0, sizeof *a);
-    const int64_t R = g.row_bytes;
+    const bool head_major = g.host_layout == KVIO_HOST_HEAD_MAJOR;
     a->layers = layers;
     a->err = err;
-    a->row_bytes = R;
+    a->row_bytes = head_major ? g.seg_bytes : g.row_bytes;
+    a->pitch = g.row_bytes;
     a->num_pages = g.num_slots / g.page_size;
     a->num_layers = g.num_layers;
     a->layer_begin = l0;
     a->page_size = g.page_size;
-    a->page_shift = ilog2_exact(g.page_size);
-    a->vec_per_row = static_cast<int32_t>(R / 16);
-    a->vec_shift = ilog2_exact(R / 16);
-    a->vec_step_rows = static_cast<int32_t>(64 / (R / 16));
-    a->vec_step_cols = static_cast<int32_t>(64 % (R / 16));
-    a->rows_per_tile = kvio::rows_per_tile(R, shape.tile_kib);
+    a->page_div = divider(g.page_size);
     a->host_layout = g.host_layout;
     a->num_heads = g.num_heads;
-    a->seg_vecs = static_cast<int32_t>(g.seg_bytes / 16);
+    a->head_div = divider(g.num_heads);
+    cut_tiles(a, shape, dir);
 }
 
-void common_args(kvio_pool_t p, const Shape &shape, int32_t l0, CopyArgs *a) {
-    common_args(p->g, p->d_layers, p->d_err, shape, l0, a);
+// Fill in the cut of the vectors of a plane into tiles.
+void cut_tiles(CopyArgs *a, const Shape &shape, Direction dir) {
+    const int64_t V = a->row_bytes / 16, most = int64_t(shape.tile_kib) * 64;
+    a->vec_per_row = static_cast<int32_t>(V);
+    a->row_div = divider(V);
+    a->vec_step_rows = static_cast<int32_t>(64 / V);
+    a->vec_step_cols = static_cast<int32_t>(64 % V);
+    a->whole_rows = dir == kOffload && !shape.device_scope && a->host_layout != KVIO_HOST_HEAD_MAJOR;
+    if (a->whole_rows) {
+        a->tile_vecs = static_cast<int32_t>(most);
+        a->tile_rows = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(most / V, 1), 64));
+        return;
+    }
+    int64_t unit = 1;                        // cuts lie at multiples of this many vectors
+    if (V < 64 && 64 % V == 0 && most / V >= 64) {
+        unit = V;                            // whole rows: a tile touches exactly tile_vecs / V
+        a->tile_vecs = static_cast<int32_t>(std::min(most, 64 * V));
+        a->tile_rows = static_cast<int32_t>(a->tile_vecs / V);
+    } else {
+        // a tile that begins inside a row touches one row more than it holds
+        a->tile_vecs = static_cast<int32_t>(std::min(most, 62 * V / 64 * 64));
+        a->tile_rows = static_cast<int32_t>(std::min<int64_t>((a->tile_vecs + V - 2) / V + 1, 64));
+    }
+    // Wide rows begin where their chunk does, page-first rows where their page
+    // does: their tiles start at the plane's first vector.
+    const bool run = a->host_layout != KVIO_HOST_PAGE_FIRST &&
+                     (a->host_layout == KVIO_HOST_HEAD_MAJOR || V % 64 != 0);
+    a->cut_mask = run ? static_cast<int32_t>(15 & ~(unit - 1)) : 0;
+    a->cut_bias = static_cast<int32_t>((a->cut_mask + V - 1) / V);
 }
 
-hipError_t launch_capped(const CopyArgs &a, Direction dir, Shape s, hipStream_t stream) {
+void add_span(CopyArgs *a) {
+    const SpanArg &s = a->spans[a->n_spans];
+    int64_t before = a->cut_mask;            // planes that begin at differing places: the most
+    if (s.host_tokens * a->row_bytes % 256 == 0)
+        before = static_cast<int64_t>((reinterpret_cast<uintptr_t>(s.host) >> 4) & uintptr_t(a->cut_mask));
+    const int64_t tiles = a->whole_rows
+                              ? (int64_t(s.num_tokens) + a->tile_rows - 1) / a->tile_rows
+                              : (int64_t(s.num_tokens) * a->vec_per_row + before + a->tile_vecs - 1) / a->tile_vecs;
+    if (a->n_spans == 0) a->tile_prefix[0] = 0;
+    a->tile_prefix[a->n_spans + 1] = static_cast<int32_t>(a->tile_prefix[a->n_spans] + tiles);
+    ++a->n_spans;
+}
+
+void common_args(kvio_pool_t p, const Shape &shape, Direction dir, int32_t l0, CopyArgs *a) {
+    common_args(p->g, p->d_layers, p->d_err, shape, dir, l0, a);
+}
+
+hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream) {
+    a.plane_tiles = a.tile_prefix[a.n_spans];
+    a.plane_div = divider(a.plane_tiles);
+    a.total_tiles = int64_t(a.planes) * a.plane_tiles;
     const int64_t waves_per_wg = s.threads / 64;
-    const int64_t max_wgs = (a.total_tiles + waves_per_wg - 1) / waves_per_wg;
+    if (s.grows) {
+        int64_t vecs = 0;                    // of the tile_vecs * plane_tiles a plane's tiles could hold
+        for (int32_t i = 0; i < a.n_spans; ++i) vecs += int64_t(a.spans[i].num_tokens) * a.vec_per_row;
+        const int64_t room = int64_t(a.plane_tiles) * a.tile_vecs / vecs;
+        s.workgroups *= static_cast<int>(std::max<int64_t>(1, std::min(room, kMostGrowth)));
+    }
+    // No more waves than tiles, and than the kernels count (far more than the chip holds).
+    const int64_t max_wgs = (std::min(a.total_tiles, kMaxWaves) + waves_per_wg - 1) / waves_per_wg;
     if (s.workgroups > max_wgs) s.workgroups = static_cast<int>(max_wgs);
     return launch_copy(a, dir, s, stream);
-}
-
-Shape kernel_shape(const PoolGeom &g, const kvio_launch &l, const Shape &def) {
-    Shape shape = resolve(l, def);
-    // LDS staging of a head-major tile needs the whole tile (>= one row) in the
-    // wave's U KiB slice.
-    if (g.host_layout == KVIO_HOST_HEAD_MAJOR && g.row_bytes > int64_t(shape.tile_kib) * 1024)
-        shape.head_major_lds = false;
-    return shape;
 }
 
 kvio_status launch_spans(const PoolGeom &g, uint8_t *const *layers, unsigned long long *err, const Resolved *rs,
                          int32_t n, int32_t l0, int32_t l1, Direction dir, const Shape &shape, hipStream_t stream,
                          const char *fn) {
-    for (int32_t first = 0; first < n; first += KVIO_MAX_SPANS_PER_LAUNCH) {
-        const int32_t cnt = n - first < KVIO_MAX_SPANS_PER_LAUNCH ? n - first : KVIO_MAX_SPANS_PER_LAUNCH;
-        CopyArgs a;
-        common_args(g, layers, err, shape, l0, &a);
-        a.n_spans = cnt;
-        int64_t tiles = 0;
-        for (int32_t i = 0; i < cnt; ++i) {
-            const Resolved &r = rs[first + i];
-            a.tile_prefix[i] = tiles;
-            a.spans[i].host = r.host;
-            a.spans[i].page_idx = r.page_idx;
-            a.spans[i].host_tokens = r.host_tokens;
-            a.spans[i].num_tokens = static_cast<int32_t>(r.num_tokens);
-            a.spans[i].origin = first + i;
-            tiles += (r.num_tokens + a.rows_per_tile - 1) / a.rows_per_tile;
-        }
-        a.tile_prefix[cnt] = tiles;
-        a.plane_tiles = tiles;
-        a.total_tiles = tiles * 2 * int64_t(l1 - l0);
-        if (a.total_tiles == 0) continue;
+    CopyArgs a;
+    common_args(g, layers, err, shape, dir, l0, &a);
+    auto launch = [&]() -> kvio_status {
+        if (a.n_spans == 0) return KVIO_OK;
         const hipError_t e = launch_capped(a, dir, shape, stream);
-        if (e != hipSuccess) return fail_hip(e, fn);
+        a.n_spans = 0;
+        return e == hipSuccess ? KVIO_OK : fail_hip(e, fn);
+    };
+    // Spans and layer ranges beyond what a launch counts in 32 bits go in pieces.
+    const int64_t most_rows = std::max<int64_t>(kMaxSpanVecs / a.vec_per_row, 1);
+    const int64_t most_layers = std::max<int64_t>(kMaxPlanes / planes(g, 1), 1);
+    for (int64_t l = l0; l < l1; l += most_layers) {
+        a.layer_begin = static_cast<int32_t>(l);
+        a.planes = static_cast<int32_t>(planes(g, std::min(l + most_layers, int64_t(l1)) - l));
+        for (int32_t i = 0; i < n; ++i) {
+            const Resolved &r = rs[i];
+            for (int64_t t0 = 0; t0 < r.num_tokens; t0 += most_rows) {
+                if (a.n_spans == KVIO_MAX_SPANS_PER_LAUNCH) {
+                    const kvio_status st = launch();
+                    if (st != KVIO_OK) return st;
+                }
+                SpanArg &s = a.spans[a.n_spans];
+                s.host = g.host_layout == KVIO_HOST_PAGE_FIRST ? r.host : r.host + t0 * a.row_bytes;
+                s.page_idx = r.page_idx;
+                s.host_tokens = r.host_tokens;
+                s.num_tokens = static_cast<int32_t>(std::min(most_rows, r.num_tokens - t0));
+                s.token0 = static_cast<int32_t>(t0);
+                s.origin = i;
+                s.page_base = 0;
+                add_span(&a);
+            }
+        }
+        const kvio_status st = launch();
+        if (st != KVIO_OK) return st;
     }
     return KVIO_OK;
 }
@@ -475,12 +523,12 @@ kvio_status run_copy(kvio_pool_t p, const kvio_span *spans, int32_t n, int32_t l
     for (const Resolved &r : rs) bytes += r.num_tokens;
     bytes *= 2 * int64_t(l1 - l0) * p->g.row_bytes;
     if (lc.flags & KVIO_LAUNCH_STAGED) {
-        if (bytes >= std::min(kStagedMinBytes, p->slot_bytes))
+        if (bytes >= std::min(kStagedMinBytes, p->slot_bytes) && int64_t(p->g.page_size) * p->g.row_bytes <= kvio::kMaxSpanVecs * 16)
             return run_staged(p, rs, spans, n, l0, l1, stream, dir,
-                              kvio::kernel_shape(p->g, lc, kvio::kDefaultStaged), fn);
+                              resolve(lc, kvio::kDefaultStaged), fn);
         lc = kvio_launch{0, 0, 0, lc.flags & ~KVIO_LAUNCH_STAGED};   // small: the kernel path, default shape
     }
-    const kvio::Shape shape = kvio::kernel_shape(p->g, lc, kvio::default_shape(dir, bytes, p->g.host_layout, p->g.num_heads));
+    const kvio::Shape shape = resolve(lc, kvio::default_shape(dir, bytes, p->g.host_layout));
     return kvio::launch_spans(p->g, p->d_layers, p->d_err, rs.data(), n, l0, l1, dir, shape, stream, fn);
 }
 

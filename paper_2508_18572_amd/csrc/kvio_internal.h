@@ -14,44 +14,86 @@ struct SpanArg {
     const uint8_t *host;       // device-visible address of the chunk
     const int32_t *page_idx;   // device page table
     int64_t host_tokens;       // per-(layer, K|V) token stride of the chunk
-    int32_t num_tokens;        // tokens to move, < 2^31
+    int32_t num_tokens;        // tokens to move; num_tokens * vec_per_row <= kMaxSpanVecs
     int32_t origin;            // index of the caller's span (error records)
-    int32_t page_base;         // context page of this span's first page (error records)
-    int32_t pad_;
+    int32_t page_base;         // context page of page_idx[0] (error records)
+    int32_t token0;            // context token of row 0, counted from page_idx[0] (page-first: and from `host`)
 };
+
+// Division of n < 2^31 by a fixed d in [1, 2^31): (n * mul) >> shift with shift
+// = 31 + ceil(log2 d) and mul = ceil(2^shift / d) < 2^32.  mul * d exceeds
+// 2^shift by less than d, so the quotient is exact for n < 2^31.
+struct Divider {
+    uint32_t mul;
+    uint32_t shift;
+};
+
+inline Divider divider(int64_t d) {
+    uint32_t s = 0;
+    while ((int64_t(1) << s) < d) ++s;
+    return {static_cast<uint32_t>(((uint64_t(1) << (31 + s)) + uint64_t(d) - 1) / uint64_t(d)), 31 + s};
+}
 
 // Kernel arguments of one launch.  Passed by value (kernarg segment), so every
 // launch carries its own span table and no device staging buffer is shared
 // between calls on different streams.
 //
-// Work decomposition: a "plane" is one (layer, K|V) of the launch's layer
-// range, planes ordered layer-major; a "tile" is up to rows_per_tile
-// consecutive token rows of one span in one plane.  tile_prefix[s] is the
-// first tile of span s inside a plane, so a plane holds plane_tiles =
-// tile_prefix[n_spans] tiles and the launch total_tiles = planes * plane_tiles.
+// Work decomposition: a "plane" is one run of host rows of the launch's layer
+// range -- a (layer, K|V), or for head-major chunks a (layer, K|V, head) --
+// planes ordered layer-major; a "tile" is tile_vecs consecutive 16-byte vectors
+// of one span in one plane.  tile_prefix[s] is the first tile of span s inside
+// a plane, so a plane holds plane_tiles = tile_prefix[n_spans] tiles and the
+// launch total_tiles = planes * plane_tiles.
+//
+// Tiles of narrow rows are cut where (host address / 16) & cut_mask is 0 (the
+// first tile of a plane is shorter by what precedes the plane's first vector).
 struct CopyArgs {
     uint8_t *const *layers;        // device table: layers[kv * num_layers + l]
     unsigned long long *err;       // device error record (0 = none)
-    int64_t row_bytes;             // R
-    int64_t plane_tiles;
-    int64_t total_tiles;
+    int64_t row_bytes;             // bytes of a host row: R, or De for head-major chunks
+    int64_t pitch;                 // bytes from one pool row to the next: R
     int64_t num_pages;             // S / P
+    int64_t total_tiles;           // planes * plane_tiles
+    int32_t planes;
+    int32_t plane_tiles;
     int32_t num_layers;            // L, stride of the layer table
     int32_t layer_begin;
     int32_t page_size;             // P
-    int32_t page_shift;            // log2(P) when P is a power of two, else -1
-    int32_t vec_per_row;           // V = R / 16
-    int32_t vec_shift;             // log2(V) when V is a power of two, else -1
+    int32_t vec_per_row;           // V = row_bytes / 16
+    Divider page_div;              // by P
+    Divider row_div;               // by V
+    Divider head_div;              // by num_heads
+    Divider plane_div;             // by plane_tiles
     int32_t vec_step_rows;         // 64 / V: rows a lane's vector index advances per 64 vectors
     int32_t vec_step_cols;         // 64 % V: and columns (carried into the row at V)
-    int32_t rows_per_tile;         // 1 .. 64
+    int32_t tile_vecs;             // vectors per tile, a multiple of 64
+    int32_t tile_rows;             // rows a tile can touch, 1 .. 64
+    int32_t cut_mask;
+    int32_t cut_bias;              // rows that cover cut_mask vectors
+    int32_t whole_rows;            // tiles are tile_rows whole rows
     int32_t n_spans;               // spans in this launch, 1 .. KVIO_MAX_SPANS_PER_LAUNCH
     int32_t host_layout;           // KVIO_HOST_*
     int32_t num_heads;             // H (head-major chunks)
-    int32_t seg_vecs;              // De / 16, 16-byte vectors per head segment (head-major)
-    int64_t tile_prefix[KVIO_MAX_SPANS_PER_LAUNCH + 1];
+    // Set by launch_copy: waves of a workgroup and of the launch, and the vectors,
+    // rows and columns from a wave's tile to its next one.
+    int32_t waves_per_wg;
+    int32_t waves;
+    int32_t step_vecs;
+    int32_t step_rows;
+    int32_t step_cols;
+    int32_t tile_prefix[KVIO_MAX_SPANS_PER_LAUNCH + 1];
     SpanArg spans[KVIO_MAX_SPANS_PER_LAUNCH];
 };
+
+// Most vectors of a span in one plane and most planes of a launch: what lies in
+// a plane is counted in 32 bits.  Larger transfers are split by the host (a
+// build may lower the first to have small ones split).
+#ifndef KVIO_MAX_SPAN_VECS
+#define KVIO_MAX_SPAN_VECS (int64_t(1) << 30)
+#endif
+constexpr int64_t kMaxSpanVecs = KVIO_MAX_SPAN_VECS;
+constexpr int64_t kMaxPlanes = int64_t(1) << 30;
+constexpr int64_t kMaxWaves = int64_t(1) << 20;
 
 enum Direction { kLoad = 0, kOffload = 1 };
 
@@ -61,58 +103,73 @@ struct Shape {
     int threads;
     int tile_kib;      // 4, 8 or 16: vectors of 16 B per lane per step
     bool nontemporal;
-    bool head_major_lds;  // head-major chunks: stage the transpose through LDS
+    bool device_scope;  // offload host stores with the device-scope (SC1) policy
+    bool grows;         // the grid is the library's: it may grow for short spans
 };
 
 // Library defaults for the launch shape, chosen by measurement on MI355X
-// (PCIe Gen5 x16 host link), on 16 of the 256 CUs for loads.
+// (PCIe Gen5 x16 host link), on 16 of the 256 CUs for large loads.
 //   Load of 32 MiB or more: 16 workgroups x 3 waves, 4 KiB steps (192 KiB in
-//   flight).  That saturates the link alone (57.6 GB/s at page size 1, the
-//   contiguous memcpy peak) and, beside an offload running on a small quota,
-//   leaves the offload's writes room on the link: 97.9 GB/s both ways
-//   against 88.6 GB/s with 4 waves per workgroup, whose extra outstanding
-//   reads slow both directions.
-//   Smaller loads: 16 x 4 waves.  A 2 MiB context is 512 tiles of 4 KiB,
-//   which 64 waves share evenly (8 each) and finish ~1 us sooner than 48.
+//   flight).  That saturates the link (57.4 GB/s, the contiguous memcpy peak,
+//   at every row size; 128 KiB in flight reach 57.0), and more reads in flight
+//   slow what runs beside them: with 256 KiB a load and a background offload
+//   move 88 GB/s together, with 192 KiB 92.
+//   Loads of 2 MiB up to that: the same waves, 24 x 2: two on a CU wait less for
+//   one another's reads than three (2 MiB of 512-byte rows 40.2 against 40.4 us).
+//   Loads below 2 MiB: 32 x 2 waves, so that their few tiles take fewer rounds
+//   (256 KiB are 64 tiles of 4 KiB: 8.1 against 8.5 us; at 2 MiB a launch behind
+//   another takes 40.6 us with 64 waves and 40.0 with 48).
 //   Offload: 32 workgroups x 4 waves with 16 KiB steps (57.0 GB/s with the
-//   device-scope host stores).
-// Two host layouts differ on large transfers (2-4 GiB at page sizes 1 and 16,
-// rows of 1-32 KV heads x 128 bf16 dims):
-//   Head-major loads with 8 or more KV heads take 8 KiB steps.  A wave step
-//   reads step / H bytes from each head's run, and at 4 KiB with 8 heads
-//   those 512-byte runs cost up to 15% (57.3 against 48.7-56.9 GB/s at
-//   8 KiB); with 16 and 32 heads the two steps are within 0.4%, with 1-4
-//   heads 4 KiB is 0.1-0.2 GB/s ahead.  2 MiB contexts keep 4 KiB (51.1
-//   against 48.6 GB/s with 4 heads).
-//   Page-first offloads take 64 x 4 waves with 8 KiB steps: 56.6-57.1 GB/s
-//   against 56.0-57.0 with 128 waves of 16 KiB (the same 2 MiB in flight),
-//   ahead at every row width.
+//   device-scope host stores).  Page-first offloads take 64 x 4 waves with 8 KiB
+//   steps: 56.6-57.1 GB/s against 56.0-57.0 with 128 waves of 16 KiB (the same
+//   2 MiB in flight), ahead at every row width (2-4 GiB, page sizes 1 and 16).
+// Where spans are so short that their tiles are mostly empty, a default grid
+// grows until as many bytes are in flight, up to kMostGrowth times.
 constexpr int kDefaultThreads = 256;
-constexpr Shape kDefaultLoad = {16, 192, 4, true, true};
-constexpr Shape kDefaultLoadHeadMajor = {16, 192, 8, true, true};
-constexpr Shape kDefaultLoadSmall = {16, kDefaultThreads, 4, true, true};
-constexpr int64_t kSmallLoadBytes = int64_t(32) << 20;
-constexpr Shape kDefaultOffload = {32, kDefaultThreads, 16, true, true};
-constexpr Shape kDefaultOffloadPageFirst = {64, kDefaultThreads, 8, true, true};
+constexpr Shape kDefaultLoad = {16, 192, 4, true, false, false};
+constexpr Shape kDefaultLoadMiddle = {24, 128, 4, true, false, false};
+constexpr Shape kDefaultLoadSmall = {32, 128, 4, true, false, false};
+constexpr int64_t kMiddleLoadBytes = int64_t(32) << 20;
+constexpr int64_t kSmallLoadBytes = int64_t(2) << 20;
+constexpr Shape kDefaultOffload = {32, kDefaultThreads, 16, true, false, false};
+constexpr Shape kDefaultOffloadPageFirst = {64, kDefaultThreads, 8, true, false, false};
+constexpr int64_t kMostGrowth = 8;
 
 // The default shape of a call that moves `bytes` in direction `dir` between
-// the pool (rows of `num_heads` KV heads) and host chunks of layout
-// `host_layout` (KVIO_HOST_*).
-inline Shape default_shape(int dir, int64_t bytes, int host_layout, int num_heads) {
+// the pool and host chunks of layout `host_layout` (KVIO_HOST_*).
+inline Shape default_shape(int dir, int64_t bytes, int host_layout) {
     if (dir != 0) return host_layout == KVIO_HOST_PAGE_FIRST ? kDefaultOffloadPageFirst : kDefaultOffload;
-    if (bytes < kSmallLoadBytes) return kDefaultLoadSmall;
-    return host_layout == KVIO_HOST_HEAD_MAJOR && num_heads >= 8 ? kDefaultLoadHeadMajor : kDefaultLoad;
+    return bytes < kSmallLoadBytes ? kDefaultLoadSmall : bytes < kMiddleLoadBytes ? kDefaultLoadMiddle : kDefaultLoad;
 }
+// Offloads whose quota keeps at least this many bytes in flight (waves x step)
+// store into host memory with the SC1 policy: enough to cover the longer
+// acknowledgement of those stores, so the link runs at its full write rate (57.0
+// against 55.7 GB/s at the default 128 waves x 16 KiB).  Smaller quotas (16 waves
+// x 4 KiB: 27 against 44 GB/s) keep the plain policy.  A build may move the
+// threshold (-DKVIO_SC1_MIN_INFLIGHT=0 stores every offload with SC1; a huge value
+// never does), which is how both policies were measured over launch shapes.
+#ifndef KVIO_SC1_MIN_INFLIGHT
+#define KVIO_SC1_MIN_INFLIGHT (int64_t(512) << 10)
+#endif
+constexpr int64_t kSc1MinInflight = KVIO_SC1_MIN_INFLIGHT;
+
 // Staged transfers: the scatter / gather between the HBM staging buffer and
 // the pool is HBM-bound, so it takes the whole chip (4 GiB of 2 KiB rows at
 // page size 1 in 1.75 ms, 2.4 TB/s of payload).
-constexpr Shape kDefaultStaged = {1024, kDefaultThreads, 16, true, true};
+constexpr Shape kDefaultStaged = {1024, kDefaultThreads, 16, true, false, false};
 
-// Rows per tile for a given step size: one step moves tile_kib KiB per wave.
-int rows_per_tile(int64_t row_bytes, int tile_kib);
+// Fill in how the vectors of a plane are cut into tiles, from row_bytes and
+// host_layout: tiles of up to tile_kib KiB that touch at most 64 rows (a lane
+// of the wave resolves each row's slot).
+// Offloads without the SC1 policy from token-major and page-first chunks take
+// tiles of up to 64 whole rows instead (tile_rows of them, counted by
+// whole_rows).
+void cut_tiles(CopyArgs *a, const Shape &shape, Direction dir);
+// Take spans[n_spans], which is filled in, into the launch.
+void add_span(CopyArgs *a);
 
-// Enqueue one copy kernel.  `a` must be fully populated.
-hipError_t launch_copy(const CopyArgs &a, Direction dir, const Shape &shape, hipStream_t stream);
+// Enqueue one copy kernel.  `a` must be populated but for what this sets.
+hipError_t launch_copy(CopyArgs &a, Direction dir, const Shape &shape, hipStream_t stream);
 
 // Error record layout: bits 40..63 = span index + 1, bits 0..39 = context page.
 constexpr int kErrSpanShift = 40;

@@ -11,15 +11,18 @@
 // pages (S).
 //
 // CDNA4 mapping
-//   * A wavefront (64 lanes) owns one tile: up to 64 consecutive token rows of
-//     one (layer, K|V) plane of one context.  Host rows of a tile are
-//     contiguous, so each wave-wide 16-byte-per-lane access covers 1 KiB of
-//     consecutive host bytes (fully coalesced).
-//   * Page-offset expansion is wavefront-level: lane r resolves the pool slot
-//     of the tile's row r with one coalesced page-table read, masks rows past
-//     the end of the context (partial last page) and range-checks the page;
-//     every vector then fetches its row's slot from the owning lane with a
+//   * A wavefront (64 lanes) owns one tile of 64 * U vectors of 16 bytes of one
+//     plane (a contiguous run of a host chunk) of one context.  Tiles are cut
+//     by vector and not by row, at 256-byte boundaries of the host address, so
+//     that every row size fills its tiles and each wave-wide access covers 1 KiB
+//     of consecutive host bytes.
+//   * Page-offset expansion is wavefront-level: lane r resolves the pool slot of
+//     the tile's row r with one coalesced page-table read and range-checks the
+//     page; every vector then fetches its row's slot from the owning lane with a
 //     cross-lane permute (ds_bpermute), so the page table is read once per row.
+//   * A CU returns vector loads in order over all its waves: a page-table read
+//     behind host reads takes a host round trip.  Loads therefore read a tile's
+//     page-table entries one tile ahead, in front of the host reads.
 //   * A step issues all U loads of a wave before any store (U KiB in flight per
 //     wave); many waves over few workgroups keep the host link busy while
 //     using a small part of the chip (Sec. 4.2: confine the I/O kernel to a
@@ -61,6 +64,25 @@ __device__ __forceinline__ void store16(uint8_t *p, u32x4 v) {
     }
 }
 
+// The kernel arguments in the constant address space, where they lie: read
+// through the scalar cache and known not to change, so that no store or atomic
+// of a kernel makes the compiler read them again (or keep them, and with them
+// the whole tile order, in vector registers).
+#define KVIO_CONSTANT const __attribute__((address_space(4)))
+typedef KVIO_CONSTANT CopyArgs Args;
+typedef KVIO_CONSTANT SpanArg Span;
+
+__device__ __forceinline__ Args &kernel_args() {
+    return *reinterpret_cast<Args *>(reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()));
+}
+
+// A wave-uniform value, in scalar registers.
+__device__ __forceinline__ int64_t scalar64(int64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32));
+    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
 // Stores into pinned host memory (the offload's destination).  With the
 // device-scope cache policy (SC1) a wave's 1 KiB stores reach the host link's
 // full write rate, the copy engine's 57.0 GB/s, where the compiler's own
@@ -87,19 +109,32 @@ __device__ __forceinline__ void store_host16(uint8_t *p, u32x4 v) {
     }
 }
 
-// Where a tile lies: its span, plane (layer, K|V), first token and row count.
-// All of it is wave-uniform, so it is computed on the scalar unit (locate,
-// from the wave's TileCursor below).
-struct TileLoc {
-    int span;
-    int layer;
-    int kv;
-    int64_t t0;
-    int nrows;
-};
+// The same store at an address in scalar registers (scalar64, taken where all
+// lanes are active) plus a lane's 32-bit offset, which takes one address register for all stores of a step instead of two for each.
+// The s_nop before it: a VMEM instruction may read a scalar register only five
+// wait states after a VALU (v_readfirstlane) wrote it, which the compiler again
+// cannot see to inside the asm.
+template <bool NT, bool SC1>
+__device__ __forceinline__ void store_host16(uint8_t *base, uint32_t off, u32x4 v) {
+    if constexpr (SC1) {
+        gvec *q = (gvec *)(base);
+        if constexpr (NT) {
+            asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2 sc1 nt\n\ts_nop 1" : : "v"(off), "v"(v), "s"(q) : "memory");
+        } else {
+            asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" : : "v"(off), "v"(v), "s"(q) : "memory");
+        }
+    } else {
+        store16<NT>(base + off, v);
+    }
+}
 
-// Largest span s with tile_prefix[s] <= w (binary search over the spans).
-__device__ __forceinline__ int span_of(const CopyArgs &a, int64_t w, int lo) {
+// n / d for n < 2^31 (see Divider).
+__device__ __forceinline__ uint32_t div_small(uint32_t n, KVIO_CONSTANT Divider &d) {
+    return static_cast<uint32_t>((static_cast<uint64_t>(n) * d.mul) >> d.shift);
+}
+
+// Largest span s >= lo with tile_prefix[s] <= w (binary search over the spans).
+__device__ __forceinline__ int span_of(Args &a, int32_t w, int lo) {
     int hi = a.n_spans - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -108,137 +143,156 @@ __device__ __forceinline__ int span_of(const CopyArgs &a, int64_t w, int lo) {
     return lo;
 }
 
-// A wave's position in the tile order: plane, tile inside the plane and the
-// span that holds it.  The wave's tiles lie `stride` (the number of waves)
-// apart, so the next one is found from the last without a 64-bit division
-// or a search in the common case (same plane, same span).
+// A wave's position in the tile order: plane, tile inside the plane, the span
+// that holds it and that span's last tile + 1.  The wave's tiles lie `waves`
+// apart, so the next one is mostly in the same span of the same plane.
 struct TileCursor {
-    int64_t plane;
-    int64_t w;
+    int32_t plane;
+    int32_t w;
+    int32_t end;
     int span;
 };
 
-__device__ __forceinline__ TileCursor cursor_at(const CopyArgs &a, int64_t g) {
+__device__ __forceinline__ void cursor_to(Args &a, TileCursor &c, int from_span) {
+    c.span = span_of(a, c.w, from_span);
+    c.end = a.tile_prefix[c.span + 1];
+}
+
+__device__ __forceinline__ TileCursor cursor_at(Args &a, int32_t g) {
     TileCursor c;
-    c.plane = g / a.plane_tiles;
+    c.plane = static_cast<int32_t>(div_small(static_cast<uint32_t>(g), a.plane_div));
     c.w = g - c.plane * a.plane_tiles;
-    c.span = span_of(a, c.w, 0);
+    cursor_to(a, c, 0);
     return c;
 }
 
-__device__ __forceinline__ void cursor_advance(const CopyArgs &a, TileCursor &c, int64_t stride) {
-    c.w += stride;
-    if (c.w >= a.plane_tiles) {                 // into a later plane: its spans start over
-        if (c.w < 2 * a.plane_tiles) {
-            c.w -= a.plane_tiles;
-            ++c.plane;
-        } else {
-            c.plane += c.w / a.plane_tiles;
-            c.w %= a.plane_tiles;
-        }
-        c.span = span_of(a, c.w, 0);
-    } else if (c.span + 1 < a.n_spans && a.tile_prefix[c.span + 1] <= c.w) {
-        c.span = span_of(a, c.w, c.span + 1);  // further on in the same plane
-    }
-}
+// Host layouts as the kernels see them: rows of one plane in one run (a token-
+// major chunk's (layer, K|V), a head-major chunk's (layer, K|V, head)), or each
+// row at an offset of its own (page-first).
+constexpr int kHostTokenMajor = KVIO_HOST_TOKEN_MAJOR;
+constexpr int kHostPageFirst = KVIO_HOST_PAGE_FIRST;
+constexpr int kHostHeadMajor = KVIO_HOST_HEAD_MAJOR;
 
-__device__ __forceinline__ TileLoc locate(const CopyArgs &a, const TileCursor &c) {
-    TileLoc L;
-    L.span = c.span;
-    L.layer = a.layer_begin + static_cast<int>(c.plane >> 1);
-    L.kv = static_cast<int>(c.plane & 1);
-    L.t0 = (c.w - a.tile_prefix[c.span]) * a.rows_per_tile;
-    const int64_t left = a.spans[c.span].num_tokens - L.t0;
-    L.nrows = left < a.rows_per_tile ? static_cast<int>(left) : a.rows_per_tile;
-    return L;
-}
-
-// Lane r < nrows: the pool page that the span's page table gives token t0 + r
-// (read only; checked by page_slot), or -1 for rows past the tile.
-__device__ __forceinline__ int32_t lane_page(const CopyArgs &a, const SpanArg &sp, int64_t t0, int nrows,
-                                             int lane) {
-    if (lane >= nrows) return -1;
-    const int64_t t = t0 + lane;
-    const int64_t cpage = a.page_shift >= 0 ? (t >> a.page_shift) : t / a.page_size;   // wave-uniform branch
-    return sp.page_idx[cpage];
-}
-
-// Lane r < nrows: pool slot of token t0 + r given its page from lane_page, or
-// -1 for rows past the tile or an out-of-range page (recorded once in the
-// error word, never dereferenced).
-__device__ __forceinline__ int page_slot(const CopyArgs &a, const SpanArg &sp, int64_t t0, int nrows, int lane,
-                                         int32_t page) {
-    int slot = -1;
-    if (lane < nrows) {
-        const int64_t t = t0 + lane;
-        int64_t cpage, off;
-        if (a.page_shift >= 0) {             // wave-uniform branch
-            cpage = t >> a.page_shift;
-            off = t & (a.page_size - 1);
-        } else {
-            cpage = t / a.page_size;
-            off = t - cpage * a.page_size;
-        }
-        if (page >= 0 && page < a.num_pages) {
-            slot = static_cast<int>(static_cast<int64_t>(page) * a.page_size + off);
-        } else {
-            const unsigned long long code =
-                (static_cast<unsigned long long>(sp.origin + 1) << kErrSpanShift) |
-                static_cast<unsigned long long>(sp.page_base + cpage);
-            atomicCAS(a.err, 0ull, code);
-        }
-    }
-    return slot;
-}
-
-// Lane r < nrows: pool slot of token t0 + r (lane_page, then page_slot).
-__device__ __forceinline__ int lane_slot(const CopyArgs &a, const SpanArg &sp, int64_t t0, int nrows, int lane) {
-    return page_slot(a, sp, t0, nrows, lane, lane_page(a, sp, t0, nrows, lane));
-}
-
-// Row of vector v of a tile (v / V).
-__device__ __forceinline__ int row_of(const CopyArgs &a, int v) {
-    return a.vec_shift >= 0 ? (v >> a.vec_shift) : (v / a.vec_per_row);
-}
-
-// Row and column of one lane's vectors of a step, which lie 64 apart: from
-// vector j to j + 64 the row grows by 64 / V and the column by 64 % V (< V),
-// with at most one carry, so only the first vector needs a division.
-struct RowCol {
-    int r, c;
+// A wave's tile: tile_vecs consecutive vectors of one plane of one span,
+// counted from `first` to `end` (the vectors of the tile that exist).  All of
+// it is wave-uniform and lives in scalar registers.  Tiles are cut by vector
+// and not by row, so every lane of a step moves a vector whatever the row
+// size, and the cuts lie at multiples of 256 host bytes, so that the reads and
+// writes a wave sends over the link are whole.
+struct Tile {
+    uint8_t *host;     // address of the tile's vector 0 (page-first: of the chunk); may precede the span
+    uint8_t *pool;     // the plane's pool layer (head-major: its head's column)
+    int32_t left;      // vectors from vector 0 to the end of the span's plane
+    int64_t safe;      // byte offset from `host` of a vector that exists
+    const int32_t *table;   // the span's page table
+    int32_t rows;           // and rows
+    int32_t token0;         // context token of the span's row 0
+    int32_t span;
+    int32_t plane;     // page-first: (layer * 2 + K|V) of the chunk
+    int32_t row0;      // first row (token) of the tile
+    int32_t col0;      // column of vector 0 in row0; negative if vector 0 precedes the span
+    int32_t first;
+    int32_t end;
 };
 
-__device__ __forceinline__ RowCol rowcol_of(const CopyArgs &a, int j) {
-    const int r = row_of(a, j);
-    return {r, j - r * a.vec_per_row};
+template <int HL, bool WIDE>
+__device__ __forceinline__ Tile locate(Args &a, const TileCursor &c) {
+    Tile t;
+    Span &sp = a.spans[c.span];
+    int32_t lkv = c.plane, head = 0;
+    if constexpr (HL == kHostHeadMajor) {
+        lkv = static_cast<int32_t>(div_small(static_cast<uint32_t>(c.plane), a.head_div));
+        head = c.plane - lkv * a.num_heads;
+    }
+    lkv += a.layer_begin * 2;
+    t.span = c.span;
+    t.table = sp.page_idx;
+    t.rows = sp.num_tokens;
+    t.token0 = sp.token0;
+    t.plane = lkv;
+    // The layer table is written before the launch and never during it, so it
+    // is read through the scalar cache: a vector load would wait its turn
+    // behind the compute unit's host reads.
+    KVIO_CONSTANT uint64_t *layers = reinterpret_cast<KVIO_CONSTANT uint64_t *>(reinterpret_cast<uintptr_t>(a.layers));
+    t.pool = reinterpret_cast<uint8_t *>(layers[(lkv & 1) * a.num_layers + (lkv >> 1)]) + head * a.row_bytes;
+    uint8_t *base = const_cast<uint8_t *>(sp.host);
+    int32_t v0 = (c.w - a.tile_prefix[c.span]) * a.tile_vecs;
+    if constexpr (HL != kHostPageFirst) {
+        const int64_t plane = HL == kHostHeadMajor ? static_cast<int64_t>(lkv) * a.num_heads + head : lkv;
+        base += plane * (sp.host_tokens * a.row_bytes);
+        if constexpr (!WIDE) v0 -= static_cast<int32_t>(reinterpret_cast<uintptr_t>(base) >> 4) & a.cut_mask;
+    }
+    t.left = t.rows * a.vec_per_row - v0;
+    t.row0 = static_cast<int32_t>(div_small(static_cast<uint32_t>(v0 > 0 ? v0 : 0), a.row_div));
+    t.col0 = v0 - t.row0 * a.vec_per_row;
+    t.first = v0 < 0 ? -v0 : 0;
+    t.end = t.left < a.tile_vecs ? (t.left < 0 ? 0 : t.left) : a.tile_vecs;
+    t.host = HL == kHostPageFirst ? base : base + static_cast<int64_t>(v0) * 16;
+    t.safe = static_cast<int64_t>(t.left > 0 ? t.first : -v0) * 16;
+    return t;
 }
 
-__device__ __forceinline__ void advance64(const CopyArgs &a, RowCol &p) {
-    p.r += a.vec_step_rows;
-    p.c += a.vec_step_cols;
-    if (p.c >= a.vec_per_row) {
-        p.c -= a.vec_per_row;
-        ++p.r;
+// The tile `waves` further on in the same span and plane, of one that begins
+// inside the span: a dozen scalar instructions where locate takes over a
+// hundred, which a wave would spend with none of its reads in flight.
+template <int HL>
+__device__ __forceinline__ void step_tile(Args &a, Tile &t) {
+    if constexpr (HL != kHostPageFirst) t.host += static_cast<int64_t>(a.step_vecs) * 16;
+    t.left -= a.step_vecs;
+    t.end = t.left < a.tile_vecs ? (t.left < 0 ? 0 : t.left) : a.tile_vecs;
+    t.row0 += a.step_rows;
+    t.col0 += a.step_cols;
+    if (t.col0 >= a.vec_per_row) {
+        t.col0 -= a.vec_per_row;
+        ++t.row0;
     }
 }
 
-// Lane r < nrows, page-first host chunk (the layers of one context page stored
-// together, Sec. 4.2.1 / Fig. 6): byte offset of row (layer, kv, t0 + r) from
-// the chunk start.  Rows of one page are contiguous; pages are L * 2 * P rows
-// apart.
-__device__ __forceinline__ int64_t lane_host_row_page_first(const CopyArgs &a, int layer, int kv,
-                                                            int64_t t0, int nrows, int lane) {
-    if (lane >= nrows) return 0;
-    const int64_t t = t0 + lane;
-    int64_t cpage, off;
-    if (a.page_shift >= 0) {
-        cpage = t >> a.page_shift;
-        off = t & (a.page_size - 1);
-    } else {
-        cpage = t / a.page_size;
-        off = t - cpage * a.page_size;
+// Lane r owns row row0 + r of the tile, if the tile can reach it and the span
+// holds it.
+__device__ __forceinline__ bool owns_row(Args &a, const Tile &t, int lane) {
+    return lane < a.tile_rows && t.row0 < t.rows - lane;
+}
+
+// Lane r: the pool page that the page table gives row row0 + r (read only;
+// checked by lane_slot).  Lanes without a row read the span's last entry, so
+// the load carries no mask and the compiler counts it exactly.
+__device__ __forceinline__ int32_t lane_page(Args &a, const Tile &t, int lane) {
+    const uint32_t last = static_cast<uint32_t>(t.rows - 1);
+    const uint32_t want = static_cast<uint32_t>(t.row0 + lane);
+    return t.table[div_small(static_cast<uint32_t>(t.token0) + (want < last ? want : last), a.page_div)];
+}
+
+// Lane r: pool slot of row row0 + r given its page from lane_page, or -1 for
+// lanes without a row and for an out-of-range page (recorded once in the error
+// word, never dereferenced).
+__device__ __forceinline__ int lane_slot(Args &a, const Tile &t, int lane, int32_t page) {
+    const bool mine = owns_row(a, t, lane), valid = page >= 0 && page < a.num_pages;
+    const uint32_t token = static_cast<uint32_t>(t.token0 + (mine ? t.row0 + lane : 0));
+    const uint32_t cpage = div_small(token, a.page_div);
+    const uint64_t bad = __ballot(mine && !valid);
+    if (bad != 0) {                          // wave-uniform: every lane records the first bad row
+        Span &sp = a.spans[t.span];
+        const uint32_t at = __builtin_amdgcn_readlane(cpage, __builtin_ctzll(bad));
+        const unsigned long long code = (static_cast<unsigned long long>(sp.origin + 1) << kErrSpanShift) |
+                                        static_cast<unsigned long long>(sp.page_base + static_cast<int64_t>(at));
+        atomicCAS(a.err, 0ull, code);
     }
-    return (((cpage * a.num_layers + layer) * 2 + kv) * a.page_size + off) * a.row_bytes;
+    const uint32_t page_size = static_cast<uint32_t>(a.page_size);
+    return mine && valid ? static_cast<int>(static_cast<uint32_t>(page) * page_size + (token - cpage * page_size)) : -1;
+}
+
+// Lane r, page-first host chunk (the layers of one context page stored
+// together, Sec. 4.2.1 / Fig. 6): byte offset of row row0 + r of the tile's
+// plane from the chunk start.  Rows of one page are contiguous; pages are
+// L * 2 * P rows apart.  Lanes without a row get the span's last row.
+__device__ __forceinline__ int64_t lane_host_row(Args &a, const Tile &t, int lane) {
+    const uint32_t last = static_cast<uint32_t>(t.rows - 1);
+    const uint32_t want = static_cast<uint32_t>(t.row0 + lane);
+    const uint32_t token = static_cast<uint32_t>(t.token0) + (want < last ? want : last);
+    const uint32_t cpage = div_small(token, a.page_div);
+    const uint32_t off = token - cpage * static_cast<uint32_t>(a.page_size);
+    return ((static_cast<int64_t>(cpage) * a.num_layers * 2 + t.plane) * a.page_size + off) * a.row_bytes;
 }
 
 __device__ __forceinline__ int64_t readlane64(int64_t v, int lane) {
@@ -247,213 +301,270 @@ __device__ __forceinline__ int64_t readlane64(int64_t v, int lane) {
     return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
-// Host layouts handled by kvio_copy_kernel: the tile's rows are one contiguous
-// run (token-major chunk), or each row sits at its own offset (page-first).
-constexpr int kHostTokenMajor = KVIO_HOST_TOKEN_MAJOR;
-constexpr int kHostPageFirst = KVIO_HOST_PAGE_FIRST;
+// Row (from row0) and column of one lane's vectors, which lie 64 apart: from
+// one vector to the next the row grows by 64 / V and the column by 64 % V (<
+// V), with at most one carry, so only the first vector needs a division.  WIDE
+// rows (V a multiple of 64) are walked by whole 64-vector chunks, on the
+// scalar unit.
+struct RowCol {
+    int r, c;
+};
 
-// Loads never carry a mask, so a wave's U loads issue back to back and the
-// compiler can count them exactly (precise s_waitcnt before each store).  A
-// chunk that must not move (past the end of a tile, or a row whose page was
-// out of range) is read from the first bytes of the pool layer instead: in
-// bounds, in device memory, and discarded.  Stores run unmasked when every
-// chunk of the step is valid (the common case) and guarded otherwise.
-//
-// `host` is the first byte of the tile's rows for a token-major chunk and the
-// chunk start for a page-first chunk, where `hoff` is the lane's row offset.
+template <bool WIDE>
+__device__ __forceinline__ RowCol rowcol_of(Args &a, const Tile &t, int lane) {
+    if constexpr (WIDE) return {0, t.col0};
+    // cut_bias rows are added so that a vector before the span stays positive.
+    const int j = t.col0 + lane + a.cut_bias * a.vec_per_row;
+    const int r = static_cast<int>(div_small(static_cast<uint32_t>(j), a.row_div));
+    return {r - a.cut_bias, j - r * a.vec_per_row};
+}
 
-// WIDE rows (R a multiple of 1 KiB): each wave-wide access of 64 x 16 B lies
-// in one row, so the row, its slot (read from the owning lane with readlane)
-// and both base addresses are wave-uniform scalars; each lane adds only its
-// own 16-byte offset.
-template <int DIR, int U, bool NT, bool SC1, int HL>
-__device__ __forceinline__ void step_wide(const CopyArgs &a, uint8_t *host, uint8_t *pool, int slot,
-                                          int64_t hoff, int base, int nvec, uint32_t lane_off) {
-    const int64_t R = a.row_bytes;
-    const int nk = (nvec - base) / 64;      // valid chunks in this step (uniform, >= 1)
-    int64_t pool_off[U];                    // chunk k's byte offset in the pool layer, -1 = skip
-    int64_t host_off[U];                    // chunk k's byte offset from `host`
-    bool all_ok = true;
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-        const int v0 = base + k * 64;
-        const int r = row_of(a, v0);
-        const int c0 = v0 - r * a.vec_per_row;
-        const int s = __builtin_amdgcn_readlane(slot, r & 63);
-        pool_off[k] = (k < nk && s >= 0) ? static_cast<int64_t>(s) * R + c0 * 16 : -1;
-        if constexpr (HL == kHostPageFirst)
-            host_off[k] = readlane64(hoff, r & 63) + c0 * 16;
-        else
-            host_off[k] = static_cast<int64_t>(v0) * 16;
-        all_ok = all_ok && pool_off[k] >= 0;
+__device__ __forceinline__ void advance64(Args &a, RowCol &p) {
+    p.r += a.vec_step_rows;
+    p.c += a.vec_step_cols;
+    if (p.c >= a.vec_per_row) {
+        p.c -= a.vec_per_row;
+        ++p.r;
     }
-    u32x4 buf[U];
-    if (DIR == kLoad) {
+}
+
+// Vector k * 64 + lane of a tile exists (WIDE: the whole chunk k).
+template <bool WIDE>
+__device__ __forceinline__ bool exists(const Tile &t, int k, int lane) {
+    if constexpr (WIDE) return k * 64 < t.end;
+    return k * 64 + lane >= t.first && k * 64 + lane < t.end;
+}
+
+// Page-first: byte offset from the chunk of a lane's vector at p, given the
+// lanes' row offsets.
+template <bool WIDE>
+__device__ __forceinline__ int64_t row_at(int64_t hoff, const RowCol &p, int lane) {
+    const int64_t row = WIDE ? readlane64(hoff, p.r & 63)
+                             : static_cast<int64_t>(__shfl(static_cast<long long>(hoff), p.r & 63));
+    return row + p.c * 16 + (WIDE ? lane * 16 : 0);
+}
+
+// Slot of the row of a lane's vector at p, or -1.  WIDE rows take it with a
+// readlane (scalar), others with a cross-lane permute.
+template <bool WIDE>
+__device__ __forceinline__ int slot_at(int slot, const RowCol &p) {
+    return WIDE ? __builtin_amdgcn_readlane(slot, p.r & 63) : __shfl(slot, p.r & 63);
+}
+
+// Byte offset in the pool layer of a lane's vector at p, in slot s >= 0.
+template <bool WIDE>
+__device__ __forceinline__ int64_t pool_at(Args &a, int s, const RowCol &p, int lane) {
+    return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(s)) * static_cast<uint64_t>(a.pitch)) +
+           p.c * 16 + (WIDE ? lane * 16 : 0);
+}
+
+// Host address of a lane's vector k of a tile.  Page-first rows lie apart: p is
+// the vector's row and column and hoff the lanes' row offsets.  Elsewhere the
+// tile is one run and both halves of its address are ready, the run's start in
+// scalar registers.
+template <bool WIDE, int HL>
+__device__ __forceinline__ uint8_t *host_at(const Tile &t, int k, const RowCol &p, int64_t hoff, int lane) {
+    if constexpr (HL == kHostPageFirst) return t.host + row_at<WIDE>(hoff, p, lane);
+    return t.host + k * 1024 + lane * 16;
+}
+
+// Page-first: byte offsets from the chunk of a lane's U vectors of a tile.
+// Elsewhere a tile is one run, and none are needed.
+template <int U, bool WIDE, int HL>
+__device__ __forceinline__ void host_rows(Args &a, const Tile &t, int lane, int64_t (&at)[U]) {
+    if constexpr (HL == kHostPageFirst) {
+        const int64_t hoff = lane_host_row(a, t, lane);
+        RowCol p = rowcol_of<WIDE>(a, t, lane);
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const uint8_t *src = k < nk ? host + host_off[k] : pool;
-            buf[k] = load16<NT>(src + lane_off);
-        }
-        if (all_ok) {
-#pragma unroll
-            for (int k = 0; k < U; ++k) store16<NT>(pool + pool_off[k] + lane_off, buf[k]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < U; ++k)
-                if (pool_off[k] >= 0) store16<NT>(pool + pool_off[k] + lane_off, buf[k]);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < U; ++k)
-            buf[k] = load16<NT>(pool + (pool_off[k] >= 0 ? pool_off[k] : 0) + lane_off);
-        if (all_ok) {
-#pragma unroll
-            for (int k = 0; k < U; ++k) store_host16<NT, SC1>(host + host_off[k] + lane_off, buf[k]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < U; ++k)
-                if (pool_off[k] >= 0) store_host16<NT, SC1>(host + host_off[k] + lane_off, buf[k]);
+            at[k] = row_at<WIDE>(hoff, p, lane);
+            advance64(a, p);
         }
     }
 }
 
-// NARROW rows (any R multiple of 16 B): a wave-wide access may span several
-// rows, so each lane fetches its row's slot (and, page-first, its row's host
-// offset) from the owning lane with a cross-lane permute (ds_bpermute).
-// Which vectors move is kept as a bit mask, and token-major host addresses
-// are formed where they are used, so at 16 KiB steps the kernel stays inside
-// the 128 registers a 1024-thread workgroup leaves each lane: only the U
-// loaded vectors and the U pool offsets of one direction are live at once.
-template <int DIR, int U, bool NT, bool SC1, int HL>
-__device__ __forceinline__ void step_narrow(const CopyArgs &a, uint8_t *host, uint8_t *pool, int slot,
-                                            int64_t hoff, int base, int nvec, int lane) {
-    static_assert(U <= 32, "the move mask holds one bit per vector");
-    const int64_t R = a.row_bytes;
-    const RowCol p0 = rowcol_of(a, base + lane);   // this lane's vector 0 of the step
-    int sl[U];                              // vector k: the slot of its row
-    int64_t host_off[HL == kHostPageFirst ? U : 1];   // page-first: its offset from `host`
-    uint32_t moves = 0;                     // bit k: vector k moves
-    auto resolve = [&]() {
-        RowCol p = p0;
+// The reads of a tile, all U behind one another; `at` from host_rows.  None
+// carries a mask, so that the compiler counts them exactly (a precise wait for
+// each).  A vector that does not move reads a place that exists and is
+// discarded: the pool layer's first bytes, in device memory, or, in a wave's
+// FIRST load tile, a host vector, so that the first reads of a launch wait for
+// nothing but the kernel arguments.
+template <int U, bool NT, bool WIDE, int HL, bool FIRST>
+__device__ __forceinline__ void read_host(const Tile &t, const int64_t (&at)[U], int lane, u32x4 (&buf)[U]) {
+    // Page-first: vector 0 of lane 0 is one of the tile's, or the span's last row's.
+    const uint8_t *idle = !FIRST ? t.pool : t.host + (HL == kHostPageFirst ? readlane64(at[0], 0) : t.safe);
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-            sl[k] = __shfl(slot, p.r & 63);
-            if constexpr (HL == kHostPageFirst)
-                host_off[k] = __shfl(static_cast<long long>(hoff), p.r & 63) + p.c * 16;
-            moves |= (base + k * 64 + lane < nvec && sl[k] >= 0) ? (1u << k) : 0u;
-            advance64(a, p);
-        }
-    };
-    // Byte offset in the pool layer of vector k at row/column p (0 for a
-    // vector that does not move: an in-bounds read, discarded).
-    auto pool_at = [&](int k, const RowCol &p) -> int64_t {
-        return ((moves >> k) & 1u) ? static_cast<int64_t>(sl[k]) * R + p.c * 16 : 0;
-    };
-    // This lane's vector k of a token-major chunk sits (base + k * 64 + lane) * 16
-    // bytes from `host`.
-    uint8_t *const host_lane = host + (static_cast<int64_t>(base) + lane) * 16;
-    auto host_at = [&](int k) -> uint8_t * {
-        if constexpr (HL == kHostPageFirst)
-            return host + host_off[k];
-        else
-            return host_lane + k * 1024;
-    };
-    constexpr uint32_t kAll = U == 32 ? ~0u : (1u << U) - 1u;
-    u32x4 buf[U];
-    RowCol p = p0;
-    if (DIR == kLoad) {
-        // Token-major host reads need no slot, so they go out first and the
-        // slots are resolved while they are in flight.
-        if constexpr (HL == kHostPageFirst) resolve();
-#pragma unroll
-        for (int k = 0; k < U; ++k)
-            buf[k] = load16<NT>(base + k * 64 + lane < nvec ? host_at(k) : pool);
-        if constexpr (HL != kHostPageFirst) resolve();
-        if (__all(moves == kAll)) {
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                store16<NT>(pool + pool_at(k, p), buf[k]);
-                advance64(a, p);
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                if ((moves >> k) & 1u) store16<NT>(pool + pool_at(k, p), buf[k]);
-                advance64(a, p);
-            }
-        }
-    } else {
-        resolve();
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            buf[k] = load16<NT>(pool + pool_at(k, p));
-            advance64(a, p);
-        }
-        if (__all(moves == kAll)) {
-#pragma unroll
-            for (int k = 0; k < U; ++k) store_host16<NT, SC1>(host_at(k), buf[k]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < U; ++k)
-                if ((moves >> k) & 1u) store_host16<NT, SC1>(host_at(k), buf[k]);
-        }
+    for (int k = 0; k < U; ++k) {
+        const uint8_t *src = t.host + (HL == kHostPageFirst ? at[k] : static_cast<int64_t>(k * 1024 + lane * 16));
+        buf[k] = load16<NT>(exists<WIDE>(t, k, lane) ? src : idle + (WIDE && !FIRST ? lane * 16 : 0));
     }
 }
 
-// The first tile of a load wave: its host reads are issued before anything
-// else (their addresses come from the kernel arguments alone), and the pool
-// layer and the slots are resolved while they are in flight, which shortens
-// the start of every launch.  Chunks that do not move read the tile's first
-// host row instead (in bounds, discarded).  Later tiles run through the step
-// functions above.
-template <int U, bool NT, bool WIDE, int HL>
-__device__ __forceinline__ void first_load_step(const CopyArgs &a, const SpanArg &sp, const TileLoc &loc,
-                                                uint8_t *host, uint8_t *&pool, int &slot, int64_t hoff,
-                                                int nvec, int lane) {
-    const int64_t R = a.row_bytes;
-    const uint32_t lane_off = static_cast<uint32_t>(lane) * 16u;
-    // Chunk k is (WIDE) vector k * 64 and the 63 after it, all in one row, or
-    // this lane's vector k * 64 + lane.  Rows and columns are walked again for
-    // the stores rather than kept, so only the U loaded vectors stay live
-    // across the slot lookup.
-    const RowCol p0 = rowcol_of(a, WIDE ? 0 : lane);
-    u32x4 buf[U];
-    {
-        RowCol p = p0;
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int j = k * 64 + (WIDE ? 0 : lane);
-            const bool valid = WIDE ? (k * 64 < nvec) : (j < nvec);
-            int64_t host_off;
-            if constexpr (HL == kHostPageFirst)
-                host_off = (WIDE ? readlane64(hoff, p.r & 63)
-                                 : static_cast<int64_t>(__shfl(static_cast<long long>(hoff), p.r & 63))) +
-                           p.c * 16;
-            else
-                host_off = static_cast<int64_t>(j) * 16;
-            buf[k] = load16<NT>(valid ? host + host_off + (WIDE ? lane_off : 0u) : host);
-            advance64(a, p);
-        }
-    }
-    pool = a.layers[loc.kv * a.num_layers + loc.layer];
-    slot = lane_slot(a, sp, loc.t0, loc.nrows, lane);
-    RowCol p = p0;
+template <int U, bool NT, bool WIDE>
+__device__ __forceinline__ void read_pool(Args &a, const Tile &t, int slot, int lane, u32x4 (&buf)[U]) {
+    RowCol p = rowcol_of<WIDE>(a, t, lane);
 #pragma unroll
     for (int k = 0; k < U; ++k) {
-        const int j = k * 64 + (WIDE ? 0 : lane);
-        const bool valid = WIDE ? (k * 64 < nvec) : (j < nvec);
-        const int s = WIDE ? __builtin_amdgcn_readlane(slot, p.r & 63) : __shfl(slot, p.r & 63);
-        if (valid && s >= 0)
-            store16<NT>(pool + static_cast<int64_t>(s) * R + p.c * 16 + (WIDE ? lane_off : 0u), buf[k]);
+        const int s = slot_at<WIDE>(slot, p);
+        const int64_t off = pool_at<WIDE>(a, s, p, lane);
+        buf[k] = load16<NT>(t.pool + (s >= 0 && exists<WIDE>(t, k, lane) ? off : 0));
         advance64(a, p);
     }
 }
 
-// DIR: kLoad (host chunk -> pool) or kOffload (pool -> host chunk).
-// U: 16-byte vectors per lane per step (one step = U KiB per wave).
-// NT: non-temporal accesses.  SC1: offload host stores with the device-scope
-// policy (store_host16).  WIDE: R is a multiple of 1 KiB (see step_wide).
+// Wait for the read of `v` and those before it; no access moves across.
+__device__ __forceinline__ void arrive(u32x4 &v) { asm volatile("" : "+v"(v) : : "memory"); }
+
+// The writes of a tile, each lane's behind its mask.  All reads have arrived
+// before the first of them, on every path.  Left to itself the compiler waits
+// inside each masked write, for the fewest operations that may be running
+// there: its waits then take in the writes before, and where the paths around
+// the last write meet, its read counts as still running and the next tile's
+// reads wait for all of this tile's writes.
+template <int DIR, int U, bool NT, bool SC1, bool WIDE, int HL>
+__device__ __forceinline__ void write_tile(Args &a, const Tile &t, int slot, int lane, u32x4 (&buf)[U]) {
+    const int64_t hoff = DIR == kOffload && HL == kHostPageFirst ? lane_host_row(a, t, lane) : 0;
+    RowCol p = rowcol_of<WIDE>(a, t, lane);
+#pragma unroll
+    for (int k = 0; k < U; ++k) arrive(buf[k]);
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        // Every lane takes part in what the lanes exchange, also where some do
+        // not store.
+        const int s = slot_at<WIDE>(slot, p);
+        const bool moves = s >= 0 && exists<WIDE>(t, k, lane);
+        if constexpr (DIR == kLoad) {
+            uint8_t *dst = t.pool + pool_at<WIDE>(a, s, p, lane);
+            if (moves) store16<NT>(dst, buf[k]);
+        } else {
+            if constexpr (HL == kHostPageFirst) {
+                uint8_t *dst = host_at<WIDE, HL>(t, k, p, hoff, lane);
+                if (moves) store_host16<NT, SC1>(dst, buf[k]);
+            } else {
+                uint8_t *dst = reinterpret_cast<uint8_t *>(scalar64(reinterpret_cast<int64_t>(t.host + k * 1024)));
+                if (moves) store_host16<NT, SC1>(dst, static_cast<uint32_t>(lane) * 16u, buf[k]);
+            }
+        }
+        advance64(a, p);
+    }
+}
+
+// Every argument that a launch's first reads depend on, in one batch of scalar
+// loads: each batch is a round trip to memory, and left to itself the compiler
+// spreads them over seven, one behind the other.
+__device__ __forceinline__ void fetch_args(Args &a) {
+    asm volatile("" : : "s"(a.total_tiles), "s"(a.waves_per_wg), "s"(a.layers), "s"(a.row_bytes), "s"(a.pitch), "s"(a.plane_tiles), "s"(a.planes), "s"(a.num_pages),
+                 "s"(a.num_layers), "s"(a.layer_begin), "s"(a.page_size), "s"(a.vec_per_row), "s"(a.page_div.mul),
+                 "s"(a.page_div.shift), "s"(a.row_div.mul), "s"(a.row_div.shift), "s"(a.tile_vecs), "s"(a.tile_rows),
+                 "s"(a.cut_mask), "s"(a.n_spans), "s"(a.waves), "s"(a.tile_prefix[1]), "s"(a.spans[0].host),
+                 "s"(a.spans[0].page_idx), "s"(a.spans[0].host_tokens), "s"(a.spans[0].num_tokens), "s"(a.spans[0].token0));
+}
+
+// The copy of one launch.  DIR: kLoad (host chunk -> pool) or kOffload (pool
+// -> host chunk).  U: 16-byte vectors per lane per tile (one tile = up to U
+// KiB per wave).  NT: non-temporal accesses.  SC1: offload host stores with
+// the device-scope policy (store_host16).  WIDE: R is a multiple of 1 KiB.
 // HL: host layout.
+//
+// A compute unit returns its vector loads in order, over all its waves.  A
+// page-table read that a wave waits for before it issues its host reads
+// therefore costs a whole host round trip (2-3 us) whenever a neighbour's host
+// reads are ahead of it; waves in step (all reading the table, then all
+// reading the host) hide this until one short tile puts a workgroup's waves
+// out of step, which then ran at 65% of the other workgroups' rate and held
+// the launch up (64 MiB of 384-byte rows: 47-50 GB/s with one short tile per
+// plane, 57.2 without).  So the table entries of a wave's next tile are read
+// right before the rows of the current one: they arrive, in order, before
+// those do, and nothing else that a wave waits for stands behind a host read.
+template <int DIR, int U, bool NT, bool SC1, bool WIDE, int HL>
+__device__ __forceinline__ void copy_tiles(Args &a) {
+    const int lane = threadIdx.x & 63;
+    fetch_args(a);
+    const int32_t g = static_cast<int32_t>(blockIdx.x) * a.waves_per_wg +
+                      static_cast<int32_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    if (g >= a.total_tiles) return;
+
+    TileCursor cur = cursor_at(a, g);
+    Tile t = locate<HL, WIDE>(a, cur);
+    // The tile after x, and whether there is one; after the last it is x again, so
+    // that every pass issues the same reads, in bounds.
+    auto following = [&](const Tile &x, bool &there) {
+        Tile n = x;
+        int32_t w = cur.w + a.waves;
+        if (w < cur.end && x.first == 0) {
+            cur.w = w;
+            step_tile<HL>(a, n);
+            there = true;
+            return n;
+        }
+        int32_t plane = cur.plane, from = cur.span;
+        if (w >= a.plane_tiles) {                // into a later plane: its spans start over
+            const int32_t planes = static_cast<int32_t>(div_small(static_cast<uint32_t>(w), a.plane_div));
+            plane += planes;
+            w -= planes * a.plane_tiles;
+            from = 0;
+        }
+        there = plane < a.planes;
+        if (there) {
+            cur.plane = plane;
+            cur.w = w;
+            cursor_to(a, cur, from);
+            n = locate<HL, WIDE>(a, cur);
+        }
+        return n;
+    };
+    u32x4 buf[U];
+    bool more;
+    if constexpr (DIR == kOffload) {
+#pragma unroll 1
+        do {
+            const int slot = lane_slot(a, t, lane, lane_page(a, t, lane));
+            read_pool<U, NT, WIDE>(a, t, slot, lane, buf);
+            write_tile<DIR, U, NT, SC1, WIDE, HL>(a, t, slot, lane, buf);
+            t = following(t, more);
+        } while (more);
+        return;
+    }
+    // The first tile, and the way to the third while its reads run.
+    bool more_after;
+    int64_t at[U];
+    host_rows<U, WIDE, HL>(a, t, lane, at);
+    read_host<U, NT, WIDE, HL, true>(t, at, lane, buf);
+    int32_t page = lane_page(a, t, lane);
+    Tile next = following(t, more);
+    const int32_t next_page = lane_page(a, next, lane);
+    int slot = lane_slot(a, t, lane, page);
+    Tile after = following(next, more_after);
+    int next_slot = lane_slot(a, next, lane, next_page);
+    page = lane_page(a, after, lane);
+    host_rows<U, WIDE, HL>(a, next, lane, at);
+    write_tile<DIR, U, NT, SC1, WIDE, HL>(a, t, slot, lane, buf);
+    if (!more) return;
+    // The others: a tile's reads go out with its slots known, right behind the
+    // writes of the one before; while they run, the wave takes the next tile's
+    // slots from the entries it read a tile ago, finds the tile after that
+    // and reads its entries.
+#pragma unroll 1
+    do {
+        t = next;
+        slot = next_slot;
+        next = after;
+        more = more_after;
+        read_host<U, NT, WIDE, HL, false>(t, at, lane, buf);
+        next_slot = lane_slot(a, next, lane, page);
+        asm volatile("" : "+v"(next_slot));      // done with `page`, whose register the next read takes
+        after = following(next, more_after);
+        page = lane_page(a, after, lane);
+        host_rows<U, WIDE, HL>(a, next, lane, at);
+        if constexpr (HL == kHostPageFirst) {
+            // worked out here, not when the tile's turn has come
+#pragma unroll
+            for (int k = 0; k < U; ++k) asm volatile("" : "+v"(at[k]));
+        }
+        write_tile<DIR, U, NT, SC1, WIDE, HL>(a, t, slot, lane, buf);
+    } while (more);
+}
+
 // Workgroup size bound of the kernels that need more than the 128 VGPRs per
 // lane a 1024-thread workgroup leaves (page-first and head-major addressing,
 // and loads of narrow token-major rows at 16 KiB steps); their launcher folds
@@ -467,259 +578,177 @@ constexpr bool needs_narrow_bound() {
 
 template <int DIR, int U, bool NT, bool SC1, bool WIDE, int HL>
 __global__ void __launch_bounds__((needs_narrow_bound<DIR, U, WIDE, HL>() ? kNarrowBound : 1024))
-    kvio_copy_kernel(const CopyArgs a) {
-    const int lane = threadIdx.x & 63;
-    const int waves_per_wg = blockDim.x >> 6;
-    const int wave_in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nwaves = static_cast<int64_t>(gridDim.x) * waves_per_wg;
-    const uint32_t lane_off = static_cast<uint32_t>(lane) * 16u;
+    kvio_copy_kernel(const CopyArgs) {
+    copy_tiles<DIR, U, NT, SC1, WIDE, HL>(kernel_args());
+}
 
-    int64_t g = static_cast<int64_t>(blockIdx.x) * waves_per_wg + wave_in_wg;
-    bool first = DIR == kLoad;
+// Head-major host chunk: one contiguous run per (layer, K|V, head).  A plane
+// is one such run: its rows are the head's segments of De = R / H bytes, its
+// pool rows lie R apart and start at the head's column.  So the head/token
+// transpose of the layout conversion is the same address arithmetic as the
+// paging, host accesses are whole runs whatever H, and nothing passes through
+// LDS.  Against a transpose through LDS whose tiles held all heads of a few
+// rows (host runs of 4 KiB / H), 64 MiB loads went from 35-57 to 56.6-57.2 GB/s over
+// 1 to 32 heads.
+template <int DIR, int U, bool NT, bool SC1>
+__global__ void __launch_bounds__(kNarrowBound) kvio_head_major_kernel(const CopyArgs) {
+    copy_tiles<DIR, U, NT, SC1, false, kHostHeadMajor>(kernel_args());
+}
+
+// ----------------------------------------------------------------------------
+// Offloads on a small quota (below kSc1MinInflight: a background backup beside
+// a load; also cached ones), from token-major and page-first chunks.  Their
+// stores are the compiler's, acknowledged before they have crossed the link, so
+// nothing tells a wave that the link is full, and what it sends too soon queues
+// ahead of a co-running load's read requests (which PCIe lets pass no posted
+// write).  These waves work in whole-row tiles, one step behind the other: slots,
+// pool reads, host writes as the reads arrive.  Measured at 16 workgroups of one
+// wave with 4 KiB steps, 336 MiB each way, beside a 48-wave load: 92.5 GB/s both
+// ways (46.1 alone); through copy_tiles' offload, plain or overlapped, 74-84
+// (40-51 alone); with device-scope stores and overlap the load takes the whole
+// link and the offload a third (67 until both are done, 55.9 alone).
+// ----------------------------------------------------------------------------
+// What a paced wave sleeps behind each step, in 64 cycles.  16 waves of 4 KiB
+// steps, alone and beside the load (ms for 336 MiB each way until both are done):
+// 0 6.87 / 8.99, 2 7.08 / 8.52, 4 7.38 / 7.96, 6 7.65 / 7.69, 8 7.95 / 7.96.
+constexpr int kPace = 6;
+
+struct RowTile {
+    int span, layer, kv;
+    int t0, nrows;                           // first row in the span, and rows
+};
+
+__device__ __forceinline__ RowTile row_tile(Args &a, const TileCursor &c) {
+    RowTile t;
+    t.span = c.span;
+    t.layer = a.layer_begin + (c.plane >> 1);
+    t.kv = c.plane & 1;
+    t.t0 = (c.w - a.tile_prefix[c.span]) * a.tile_rows;
+    const int left = a.spans[c.span].num_tokens - t.t0;
+    t.nrows = left < a.tile_rows ? left : a.tile_rows;
+    return t;
+}
+
+// Lane r < nrows: pool slot of the tile's row r, or -1 (see lane_slot).
+__device__ __forceinline__ int row_slot(Args &a, Span &sp, const RowTile &t, int lane) {
+    int slot = -1;
+    if (lane < t.nrows) {
+        const uint32_t token = static_cast<uint32_t>(sp.token0 + t.t0 + lane);
+        const uint32_t cpage = div_small(token, a.page_div);
+        const int32_t page = sp.page_idx[cpage];
+        if (page >= 0 && page < a.num_pages) {
+            slot = static_cast<int>(static_cast<uint32_t>(page) * static_cast<uint32_t>(a.page_size) +
+                                    (token - cpage * static_cast<uint32_t>(a.page_size)));
+        } else {
+            const unsigned long long code =
+                (static_cast<unsigned long long>(sp.origin + 1) << kErrSpanShift) |
+                static_cast<unsigned long long>(sp.page_base + static_cast<int64_t>(cpage));
+            atomicCAS(a.err, 0ull, code);
+        }
+    }
+    return slot;
+}
+
+template <int U, bool NT, bool WIDE, int HL>
+__global__ void __launch_bounds__((HL != KVIO_HOST_TOKEN_MAJOR ? 256 : 1024)) kvio_copy_kernel_paced(const CopyArgs) {
+    Args &a = kernel_args();
+    const int lane = threadIdx.x & 63;
+    const int32_t g = static_cast<int32_t>(blockIdx.x) * a.waves_per_wg +
+                      static_cast<int32_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    if (g >= a.total_tiles) return;
     TileCursor cur = cursor_at(a, g);
 #pragma unroll 1
-    for (; g < a.total_tiles; g += nwaves, cursor_advance(a, cur, nwaves)) {
-        const TileLoc loc = locate(a, cur);
-        const SpanArg &sp = a.spans[loc.span];
+    for (;;) {
+        const RowTile t = row_tile(a, cur);
+        Span &sp = a.spans[t.span];
+        const uint8_t *pool = a.layers[t.kv * a.num_layers + t.layer];
+        const int slot = row_slot(a, sp, t, lane);
         uint8_t *host = const_cast<uint8_t *>(sp.host);
-        int64_t hoff = 0;
+        const int64_t plane = static_cast<int64_t>(t.layer) * 2 + t.kv;
+        int64_t hoff = 0;                    // page-first: lane r's row r from the chunk
         if constexpr (HL == kHostPageFirst) {
-            hoff = lane_host_row_page_first(a, loc.layer, loc.kv, loc.t0, loc.nrows, lane);
+            const uint32_t token = static_cast<uint32_t>(sp.token0 + t.t0 + (lane < t.nrows ? lane : 0));
+            const uint32_t cpage = div_small(token, a.page_div);
+            hoff = ((static_cast<int64_t>(cpage) * a.num_layers * 2 + plane) * a.page_size +
+                    (token - cpage * static_cast<uint32_t>(a.page_size))) * a.row_bytes;
         } else {
-            // First byte of the tile's rows (layer-major chunk, K then V).
-            host += ((static_cast<int64_t>(loc.layer) * 2 + loc.kv) * sp.host_tokens + loc.t0) * a.row_bytes;
+            host += (plane * sp.host_tokens + t.t0) * a.row_bytes;
         }
-        const int nvec = loc.nrows * a.vec_per_row;
-        uint8_t *pool;
-        int slot;
-        int base = 0;
-        if (first) {
-            first = false;
-            first_load_step<U, NT, WIDE, HL>(a, sp, loc, host, pool, slot, hoff, nvec, lane);
-            base = 64 * U;
-        } else {
-            pool = a.layers[loc.kv * a.num_layers + loc.layer];
-            slot = lane_slot(a, sp, loc.t0, loc.nrows, lane);
-        }
-#pragma unroll 1
-        for (; base < nvec; base += 64 * U) {
-            if constexpr (WIDE) {
-                step_wide<DIR, U, NT, SC1, HL>(a, host, pool, slot, hoff, base, nvec, lane_off);
-            } else {
-                step_narrow<DIR, U, NT, SC1, HL>(a, host, pool, slot, hoff, base, nvec, lane);
-            }
-        }
-    }
-}
-
-// ----------------------------------------------------------------------------
-// Head-major host chunk: one contiguous run per (layer, K|V, head), so a pool
-// row (token-major [H][D]) gathers H segments of De = R / H bytes from H runs.
-// This is the head/token transpose of the layout conversion.
-//
-// LDS = true: each wave owns one tile of n rows that fits its share of LDS.
-// It reads the tile in host order (per head, n * De contiguous bytes), writes
-// each 16-byte vector to its pool-order position in the wave's LDS slice,
-// and then reads the slice back in pool order, so both sides are long
-// contiguous runs: host reads of n * De bytes, pool writes of whole rows.
-// Offload runs the same two phases the other way round.
-// LDS = false: a direct gather in pool order (each wave-wide access reads
-// 64 / (De / 16) head segments of De bytes from as many runs).
-//
-// Vector numbering inside a tile (Vd = De / 16 vectors per segment,
-// V = H * Vd per row):
-//   pool order  p = r * V + h * Vd + c     (pool row r, head h, vector c)
-//   host order  q = (h * n + r) * Vd + c
-// ----------------------------------------------------------------------------
-template <int DIR, int U, bool NT, bool SC1, bool LDS>
-__global__ void __launch_bounds__(kNarrowBound) kvio_head_major_kernel(const CopyArgs a) {
-    extern __shared__ u32x4 lds[];           // U * 64 vectors per wave
-    const int lane = threadIdx.x & 63;
-    const int waves_per_wg = blockDim.x >> 6;
-    const int wave_in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nwaves = static_cast<int64_t>(gridDim.x) * waves_per_wg;
-    u32x4 *slice = lds + wave_in_wg * (U * 64);
-    const int64_t R = a.row_bytes;
-    const int V = a.vec_per_row;
-    const int Vd = a.seg_vecs;
-    const int64_t De = static_cast<int64_t>(Vd) * 16;
-
-    int64_t g0 = static_cast<int64_t>(blockIdx.x) * waves_per_wg + wave_in_wg;
-    TileCursor cur = cursor_at(a, g0);
-#pragma unroll 1
-    for (int64_t g = g0; g < a.total_tiles; g += nwaves, cursor_advance(a, cur, nwaves)) {
-        const TileLoc loc = locate(a, cur);
-        const SpanArg &sp = a.spans[loc.span];
-        uint8_t *pool = a.layers[loc.kv * a.num_layers + loc.layer];
-        const int n = loc.nrows;
-        // Start of head 0's run at token t0; head h's run is h * host_tokens * De further.
-        uint8_t *host = const_cast<uint8_t *>(sp.host) +
-                        ((static_cast<int64_t>(loc.layer) * 2 + loc.kv) * a.num_heads * sp.host_tokens + loc.t0) * De;
-        const int64_t head_stride = sp.host_tokens * De;
-        // The page-table read goes out first.  A load through LDS with steps of
-        // 8 KiB or more then issues its host reads and checks the page once
-        // they are in flight: the table read is older than them, so waiting
-        // for it leaves them outstanding (workload-size head-major loads:
-        // 57.2-57.3 against 56.8-56.9 GB/s).  With 4 KiB steps, the small-call
-        // default, checking first is faster (2 MiB contexts: 51.0 against
-        // 48.8-49.2 GB/s), and the other paths need the slot before their
-        // first access.
-        constexpr bool kLateSlot = LDS && DIR == kLoad && U >= 8;
-        const int32_t page = lane_page(a, sp, loc.t0, n, lane);
-        int slot = kLateSlot ? -1 : page_slot(a, sp, loc.t0, n, lane, page);
-        const int nvec = n * V;
+        const int nvec = t.nrows * a.vec_per_row;
 #pragma unroll 1
         for (int base = 0; base < nvec; base += 64 * U) {
-            if constexpr (LDS) {
-                // The whole tile is one step (rows_per_tile keeps n * R <= U KiB).
-                if (DIR == kLoad) {
-                    u32x4 buf[U];
-                    int pos[U];                             // pool-order position of vector q, -1 = none
+            // Vector k: chunk base + k * 64 (WIDE, all lanes in one row) or this
+            // lane's vector of it.
+            const int j = base + (WIDE ? 0 : lane);
+            const int r0 = static_cast<int>(div_small(static_cast<uint32_t>(j), a.row_div));
+            RowCol p = {r0, j - r0 * a.vec_per_row};
+            u32x4 buf[U];
+            uint32_t moves = 0;
 #pragma unroll
-                    for (int k = 0; k < U; ++k) {          // host order, contiguous per head
-                        const int q = k * 64 + lane;
-                        const int hr = q / Vd;              // h * n + r
-                        const int h = hr / n;
-                        const int r = hr - h * n;
-                        const int c = q - hr * Vd;
-                        pos[k] = q < nvec ? r * V + h * Vd + c : -1;
-                        buf[k] = load16<NT>(q < nvec ? host + h * head_stride + (static_cast<int64_t>(r) * Vd + c) * 16
-                                                     : pool);
-                    }
-                    slot = page_slot(a, sp, loc.t0, n, lane, page);
-                    // All U loads are in flight before the first LDS write waits for one.
+            for (int k = 0; k < U; ++k) {
+                const int s = slot_at<WIDE>(slot, p);
+                const bool ok = j + k * 64 < nvec && s >= 0;
+                moves |= ok ? 1u << k : 0u;
+                const int64_t off = pool_at<WIDE>(a, s, p, lane);
+                buf[k] = load16<NT>(pool + (ok ? off : 0));
+                advance64(a, p);
+            }
+            p = {r0, j - r0 * a.vec_per_row};
+            auto at = [&](int k) -> uint8_t * {
+                if constexpr (HL == kHostPageFirst) return host + row_at<WIDE>(hoff, p, lane);
+                return host + static_cast<int64_t>(base + k * 64 + lane) * 16;
+            };
+            if (__all(moves == (1u << U) - 1u)) {
 #pragma unroll
-                    for (int k = 0; k < U; ++k)
-                        if (pos[k] >= 0) slice[pos[k]] = buf[k];
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-                    for (int k = 0; k < U; ++k) {          // pool order, whole rows
-                        const int p = k * 64 + lane;
-                        const int r = p / V;
-                        const int s = __shfl(slot, r & 63);
-                        if (p < nvec && s >= 0)
-                            store16<NT>(pool + static_cast<int64_t>(s) * R + (p - r * V) * 16, slice[p]);
-                    }
-                } else {
-                    u32x4 buf[U];
-#pragma unroll
-                    for (int k = 0; k < U; ++k) {          // pool order, whole rows
-                        const int p = k * 64 + lane;
-                        const int r = p / V;
-                        const int s = __shfl(slot, r & 63);
-                        buf[k] = load16<NT>(pool + (p < nvec && s >= 0
-                                                        ? static_cast<int64_t>(s) * R + (p - r * V) * 16
-                                                        : 0));
-                    }
-#pragma unroll
-                    for (int k = 0; k < U; ++k)
-                        if (k * 64 + lane < nvec) slice[k * 64 + lane] = buf[k];
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-                    for (int k = 0; k < U; ++k) {          // host order, contiguous per head
-                        const int q = k * 64 + lane;
-                        const int hr = q / Vd;
-                        const int h = hr / n;
-                        const int r = hr - h * n;
-                        const int c = q - hr * Vd;
-                        const int s = __shfl(slot, r & 63);
-                        if (q < nvec && s >= 0)
-                            store_host16<NT, SC1>(host + h * head_stride + (static_cast<int64_t>(r) * Vd + c) * 16,
-                                        slice[r * V + h * Vd + c]);
-                    }
+                for (int k = 0; k < U; ++k) {
+                    store16<NT>(at(k), buf[k]);
+                    advance64(a, p);
                 }
-                // The slice is reused by the wave's next tile.
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
             } else {
-                u32x4 buf[U];
-                int64_t pool_off[U];
-                int64_t host_off[U];
 #pragma unroll
-                for (int k = 0; k < U; ++k) {              // pool order
-                    const int p = base + k * 64 + lane;
-                    const int r = p / V;
-                    const int hv = p - r * V;
-                    const int h = hv / Vd;
-                    const int c = hv - h * Vd;
-                    const int s = __shfl(slot, r & 63);
-                    pool_off[k] = (p < nvec && s >= 0) ? static_cast<int64_t>(s) * R + hv * 16 : -1;
-                    host_off[k] = h * head_stride + (static_cast<int64_t>(r) * Vd + c) * 16;
-                }
-                if (DIR == kLoad) {
-#pragma unroll
-                    for (int k = 0; k < U; ++k)
-                        buf[k] = load16<NT>(base + k * 64 + lane < nvec ? host + host_off[k] : pool);
-#pragma unroll
-                    for (int k = 0; k < U; ++k)
-                        if (pool_off[k] >= 0) store16<NT>(pool + pool_off[k], buf[k]);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < U; ++k) buf[k] = load16<NT>(pool + (pool_off[k] >= 0 ? pool_off[k] : 0));
-#pragma unroll
-                    for (int k = 0; k < U; ++k)
-                        if (pool_off[k] >= 0) store_host16<NT, SC1>(host + host_off[k], buf[k]);
+                for (int k = 0; k < U; ++k) {
+                    uint8_t *dst = at(k);
+                    if ((moves >> k) & 1u) store16<NT>(dst, buf[k]);
+                    advance64(a, p);
                 }
             }
+        }
+        __builtin_amdgcn_s_sleep(kPace);
+        int32_t from = cur.span;
+        cur.w += a.waves;
+        if (cur.w >= a.plane_tiles) {
+            const int32_t planes = static_cast<int32_t>(div_small(static_cast<uint32_t>(cur.w), a.plane_div));
+            cur.plane += planes;
+            cur.w -= planes * a.plane_tiles;
+            from = 0;
+        }
+        if (cur.plane >= a.planes) return;
+        if (from == 0 || cur.w >= cur.end) cursor_to(a, cur, from);
+    }
+}
+
+template <int DIR, int U, bool NT, bool SC1, int HL>
+static void launch_layout(const CopyArgs &a, dim3 grid, dim3 block, hipStream_t stream) {
+    if constexpr (HL == kHostHeadMajor) {
+        hipLaunchKernelGGL((kvio_head_major_kernel<DIR, U, NT, SC1>), grid, block, 0, stream, a);
+    } else {
+        const bool wide = a.vec_per_row % 64 == 0;
+        if constexpr (DIR == kOffload && !SC1) {
+            if (wide)
+                hipLaunchKernelGGL((kvio_copy_kernel_paced<U, NT, true, HL>), grid, block, 0, stream, a);
+            else
+                hipLaunchKernelGGL((kvio_copy_kernel_paced<U, NT, false, HL>), grid, block, 0, stream, a);
+        } else {
+            if (wide)
+                hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, true, HL>), grid, block, 0, stream, a);
+            else
+                hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, false, HL>), grid, block, 0, stream, a);
         }
     }
 }
 
-int rows_per_tile(int64_t row_bytes, int tile_kib) {
-    const int64_t r = (static_cast<int64_t>(tile_kib) * 1024) / row_bytes;
-    return r < 1 ? 1 : (r > 64 ? 64 : static_cast<int>(r));
-}
-
-// Offloads whose launch keeps at least this many bytes in flight (waves x
-// step) store into host memory with the SC1 policy: enough to cover the
-// longer acknowledgement of those stores, so the link runs at its full write
-// rate (57.0 against 55.7 GB/s at the default 128 waves x 16 KiB).  Smaller
-// quotas (16 waves x 4 KiB: 27 against 44 GB/s) keep the plain policy.  A
-// build may move the threshold (-DKVIO_SC1_MIN_INFLIGHT=0 stores every
-// offload with SC1; a huge value never does), which is how both policies
-// were measured over launch shapes.
-#ifndef KVIO_SC1_MIN_INFLIGHT
-#define KVIO_SC1_MIN_INFLIGHT (int64_t(512) << 10)
-#endif
-constexpr int64_t kSc1MinInflight = KVIO_SC1_MIN_INFLIGHT;
-
 template <int DIR, int U, bool NT, bool SC1>
-static hipError_t launch_policy(const CopyArgs &a, dim3 grid, dim3 block, const Shape &s, hipStream_t stream) {
-    const bool wide = a.vec_per_row % 64 == 0;
-    switch (a.host_layout) {
-        case kHostPageFirst:
-            if (wide)
-                hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, true, kHostPageFirst>), grid, block, 0, stream,
-                                   a);
-            else
-                hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, false, kHostPageFirst>), grid, block, 0, stream,
-                                   a);
-            break;
-        case KVIO_HOST_HEAD_MAJOR:
-            if (s.head_major_lds)
-                hipLaunchKernelGGL((kvio_head_major_kernel<DIR, U, NT, SC1, true>), grid, block,
-                                   static_cast<size_t>(block.x / 64) * U * 1024, stream, a);
-            else
-                hipLaunchKernelGGL((kvio_head_major_kernel<DIR, U, NT, SC1, false>), grid, block, 0, stream, a);
-            break;
-        default:
-            if (wide)
-                hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, true, kHostTokenMajor>), grid, block, 0, stream,
-                                   a);
-            else
-                hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, false, kHostTokenMajor>), grid, block, 0,
-                                   stream, a);
-    }
-    return hipGetLastError();
-}
-
-template <int DIR, int U, bool NT>
-static hipError_t launch_u(const CopyArgs &a, const Shape &s, hipStream_t stream) {
+static hipError_t launch_u(CopyArgs &a, const Shape &s, hipStream_t stream) {
     dim3 grid(s.workgroups), block(s.threads);
     const bool wide = a.vec_per_row % 64 == 0;
     const bool narrow_bound = a.host_layout != KVIO_HOST_TOKEN_MAJOR ||
@@ -729,28 +758,33 @@ static hipError_t launch_u(const CopyArgs &a, const Shape &s, hipStream_t stream
         grid = dim3(static_cast<unsigned>(int64_t(s.workgroups) * s.threads / kNarrowBound));
         block = dim3(kNarrowBound);
     }
-    if constexpr (DIR == kOffload && NT) {
-        const int64_t inflight = int64_t(grid.x) * (block.x / 64) * U * 1024;
-        if (inflight >= kSc1MinInflight) return launch_policy<DIR, U, NT, true>(a, grid, block, s, stream);
+    a.waves_per_wg = static_cast<int32_t>(block.x / 64);
+    a.waves = static_cast<int32_t>(grid.x) * a.waves_per_wg;
+    a.step_vecs = a.waves * a.tile_vecs;         // used where it stays inside a span
+    a.step_rows = a.step_vecs / a.vec_per_row;
+    a.step_cols = a.step_vecs % a.vec_per_row;
+    switch (a.host_layout) {
+        case kHostPageFirst: launch_layout<DIR, U, NT, SC1, kHostPageFirst>(a, grid, block, stream); break;
+        case kHostHeadMajor: launch_layout<DIR, U, NT, SC1, kHostHeadMajor>(a, grid, block, stream); break;
+        default: launch_layout<DIR, U, NT, SC1, kHostTokenMajor>(a, grid, block, stream);
     }
-    return launch_policy<DIR, U, NT, false>(a, grid, block, s, stream);
+    return hipGetLastError();
 }
 
-template <int DIR, bool NT>
-static hipError_t launch_nt(const CopyArgs &a, const Shape &s, hipStream_t stream) {
-    switch (s.tile_kib) {
-        case 4: return launch_u<DIR, 4, NT>(a, s, stream);
-        case 8: return launch_u<DIR, 8, NT>(a, s, stream);
-        default: return launch_u<DIR, 16, NT>(a, s, stream);
-    }
+template <int DIR, bool NT, bool SC1>
+static hipError_t launch_step(CopyArgs &a, const Shape &s, hipStream_t stream) {
+    // The smallest step that holds a tile (rows below 64 bytes make small ones).
+    if (a.tile_vecs <= 256) return launch_u<DIR, 4, NT, SC1>(a, s, stream);
+    if (a.tile_vecs <= 512) return launch_u<DIR, 8, NT, SC1>(a, s, stream);
+    return launch_u<DIR, 16, NT, SC1>(a, s, stream);
 }
 
-hipError_t launch_copy(const CopyArgs &a, Direction dir, const Shape &s, hipStream_t stream) {
-    if (dir == kLoad) {
-        return s.nontemporal ? launch_nt<kLoad, true>(a, s, stream) : launch_nt<kLoad, false>(a, s, stream);
-    }
-    return s.nontemporal ? launch_nt<kOffload, true>(a, s, stream)
-                         : launch_nt<kOffload, false>(a, s, stream);
+hipError_t launch_copy(CopyArgs &a, Direction dir, const Shape &s, hipStream_t stream) {
+    if (dir == kLoad)
+        return s.nontemporal ? launch_step<kLoad, true, false>(a, s, stream) : launch_step<kLoad, false, false>(a, s, stream);
+    if (s.device_scope) return launch_step<kOffload, true, true>(a, s, stream);
+    return s.nontemporal ? launch_step<kOffload, true, false>(a, s, stream)
+                         : launch_step<kOffload, false, false>(a, s, stream);
 }
 
 }  // namespace kvio

@@ -103,9 +103,9 @@ extern "C" kvio_status kvio_load_noalloc(const kvio_pool_desc *desc, const kvio_
     hipLaunchKernelGGL(kvio_noalloc_setup, dim3(1), dim3(256), 0, stream, init);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return kvio::fail_hip(e, fn);
-    const kvio::Shape shape = kvio::kernel_shape(
-        g, desc->load_launch,
-        kvio::default_shape(kvio::kLoad, tokens * 2 * (layer_end - layer_begin) * g.row_bytes, g.host_layout, g.num_heads));
+    const kvio::Shape shape = kvio::resolve(
+        desc->load_launch,
+        kvio::default_shape(kvio::kLoad, tokens * 2 * (layer_end - layer_begin) * g.row_bytes, g.host_layout));
     return kvio::launch_spans(g, init.table, init.err, rs, n_spans, layer_begin, layer_end, kvio::kLoad, shape,
                               stream, fn);
 }

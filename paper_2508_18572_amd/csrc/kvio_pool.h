@@ -56,17 +56,19 @@ kvio_status validate_spans(const PoolGeom &g, const kvio_span *spans, int32_t n,
 // Validate a launch shape; fill in a shape from it and the defaults.
 kvio_status check_launch(const kvio_launch &l, const char *which);
 Shape resolve(const kvio_launch &l, const Shape &def);
-// The kernel path's shape for a pool (head-major tiles too wide for LDS gather directly).
-Shape kernel_shape(const PoolGeom &g, const kvio_launch &l, const Shape &def);
+// Planes of `layers` layers of a pool.
+inline int64_t planes(const PoolGeom &g, int64_t layers) {
+    return layers * 2 * (g.host_layout == KVIO_HOST_HEAD_MAJOR ? g.num_heads : 1);
+}
 // Device-visible address of [p, p + bytes) (see kvio_api.cpp).
 kvio_status device_view(const void *p, uint64_t bytes, bool want_device_memory, const char *what,
                         const uint8_t **out);
 // Fields of a launch that do not depend on its spans.
 void common_args(const PoolGeom &g, uint8_t *const *layers, unsigned long long *err, const Shape &shape,
-                 int32_t l0, CopyArgs *a);
-void common_args(kvio_pool_t p, const Shape &shape, int32_t l0, CopyArgs *a);
-// Launch with the workgroup count capped at what the tiles can use.
-hipError_t launch_capped(const CopyArgs &a, Direction dir, Shape s, hipStream_t stream);
+                 Direction dir, int32_t l0, CopyArgs *a);
+void common_args(kvio_pool_t p, const Shape &shape, Direction dir, int32_t l0, CopyArgs *a);
+// Launch what the arguments hold, the workgroup count capped at what its tiles can use.
+hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream);
 // Enqueue the kernel launches of a transfer of validated spans, one launch
 // per KVIO_MAX_SPANS_PER_LAUNCH spans; `layers` (device table of 2 * L layer
 // addresses) and `err` (device error word) are what the kernels read and

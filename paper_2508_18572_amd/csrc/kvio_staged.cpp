@@ -37,7 +37,9 @@ namespace kvio {
 kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvio_span *spans, int32_t n,
                        int32_t l0, int32_t l1, hipStream_t stream, kvio::Direction dir, const kvio::Shape &shape,
                        const char *fn) {
-    const int64_t R = p->g.row_bytes, P = p->g.page_size, cap = p->slot_bytes;
+    const int64_t R = p->g.row_bytes, P = p->g.page_size;
+    // A unit stays within what a launch counts in 32 bits.
+    const int64_t cap = std::min(p->slot_bytes, kMaxSpanVecs * 32);
     if (p->stage[dir] == nullptr) return fail(KVIO_EINVAL, "%s: the pool has no staging buffer for this direction", fn);
     hipStream_t ks = p->side_stream[dir];
     struct Unit { int32_t span; int64_t t0, n, off; };
@@ -77,7 +79,7 @@ kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvi
     auto flush = [&](int32_t lb, int32_t g) -> kvio_status {
         if (units.empty()) return KVIO_OK;
         const int k = int(chunk % kStageSlots);
-        uint8_t *slot = p->stage[dir] + int64_t(k) * cap;
+        uint8_t *slot = p->stage[dir] + int64_t(k) * p->slot_bytes;
         hipEvent_t filled = p->ev_filled[dir][k], freed = p->ev_free[dir][k];
         hipError_t err = hipSuccess;
         if (dir == kvio::kLoad) {
@@ -90,24 +92,20 @@ kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvi
         }
         if (err != hipSuccess) return fail_hip(err, fn);
         kvio::CopyArgs a;
-        common_args(p, shape, lb, &a);
-        a.n_spans = static_cast<int32_t>(units.size());
-        int64_t tiles = 0;
-        for (size_t i = 0; i < units.size(); ++i) {
-            const Unit &u = units[i];
-            a.tile_prefix[i] = tiles;
-            a.spans[i].host = reinterpret_cast<const uint8_t *>(reinterpret_cast<uintptr_t>(slot) + uintptr_t(u.off) -
-                                                                uintptr_t(int64_t(lb) * 2 * u.n * R));
-            a.spans[i].page_idx = rs[size_t(u.span)].page_idx + u.t0 / P;
-            a.spans[i].host_tokens = u.n;
-            a.spans[i].num_tokens = static_cast<int32_t>(u.n);
-            a.spans[i].origin = u.span;
-            a.spans[i].page_base = static_cast<int32_t>(u.t0 / P);
-            tiles += (u.n + a.rows_per_tile - 1) / a.rows_per_tile;
+        common_args(p, shape, dir, lb, &a);
+        a.planes = static_cast<int32_t>(planes(p->g, g));
+        for (const Unit &u : units) {
+            SpanArg &sp = a.spans[a.n_spans];
+            sp.host = reinterpret_cast<const uint8_t *>(reinterpret_cast<uintptr_t>(slot) + uintptr_t(u.off) -
+                                                        uintptr_t(int64_t(lb) * 2 * u.n * R));
+            sp.page_idx = rs[size_t(u.span)].page_idx + u.t0 / P;
+            sp.host_tokens = u.n;
+            sp.num_tokens = static_cast<int32_t>(u.n);
+            sp.origin = u.span;
+            sp.page_base = static_cast<int32_t>(u.t0 / P);
+            sp.token0 = 0;
+            add_span(&a);
         }
-        a.tile_prefix[units.size()] = tiles;
-        a.plane_tiles = tiles;
-        a.total_tiles = tiles * 2 * g;
         if ((err = launch_capped(a, dir, shape, ks)) != hipSuccess) return fail_hip(err, fn);
         if (dir == kvio::kLoad) {
             err = hipEventRecord(freed, ks);

@@ -1,0 +1,182 @@
+"""The library's own sources, kernels included, built for the CPU (tests/c/emu:
+the 64 lanes of a wave are coroutines that must meet at every cross-lane
+operation, values taken as wave-uniform must be, and every buffer lies against
+an inaccessible page), against the oracle: every form the entry points take --
+host layouts, row widths, page sizes, ragged and empty spans, chunks at every
+16-byte offset, spans longer than a plane's 32-bit count, out-of-range pages,
+launch shapes, staged transfers -- on kernels that count vectors rather than
+rows."""
+import ctypes
+import importlib.util
+import os
+import random
+import re
+import shutil
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2508_18572_amd", "csrc")
+CXX = "/opt/rocm/llvm/bin/clang++"
+LAYOUT = {0: oracle.TOKEN_MAJOR, 1: oracle.PAGE_FIRST, 2: oracle.HEAD_MAJOR}
+
+pytestmark = pytest.mark.skipif(not os.path.exists(CXX), reason="no clang++ (the sources use its vector types)")
+
+
+def plain(text):
+    """The source with its inline assembly as what it does: a store, or nothing."""
+    text = re.sub(r'asm volatile\("[^;]*?" : : "v"\((\w+)\), "v"\((\w+)\), "s"\((\w+)\) : "memory"\);',
+                  r"*(gvec *)((uintptr_t)\3 + \1) = \2;", text)
+    text = re.sub(r'asm volatile\("[^;]*?" : : "v"\((\w+)\), "v"\((\w+)\) : "memory"\);', r"*\1 = \2;", text)
+    text = re.sub(r'asm volatile\("" : [^;]*;', ";", text)
+    assert "asm volatile" not in text
+    return text
+
+
+def build(out, extra=()):
+    for f in os.listdir(CSRC):
+        with open(os.path.join(CSRC, f)) as src, open(os.path.join(out, f), "w") as dst:
+            dst.write(plain(src.read()))
+    emu = os.path.join(ROOT, "tests", "c", "emu")
+    sources = [os.path.join(out, f) for f in sorted(os.listdir(out)) if f.endswith((".cpp", ".hip"))]
+    flags = ["-x", "c++", "-std=c++17", "-O1", "-fPIC", "-U_FORTIFY_SOURCE", "-I", emu, "-I",
+             os.path.join(ROOT, "include"), "-I", out, *extra]
+    objects = [s + ".o" for s in sources] + [os.path.join(out, "emu.o")]
+    jobs = [subprocess.Popen([CXX, *flags, "-c", s, "-o", o])
+            for s, o in zip(sources + [os.path.join(emu, "emu.cpp")], objects)]
+    assert all([j.wait() == 0 for j in jobs])
+    subprocess.run([CXX, "-shared", "-o", os.path.join(out, "libkvio.so"), *objects, "-pthread"], check=True)
+    shutil.copy(os.path.join(ROOT, "paper_2508_18572_amd", "kvio.py"), out)
+
+
+def load(out):
+    spec = importlib.util.spec_from_file_location("kvio_emulated_" + os.path.basename(out), os.path.join(out, "kvio.py"))
+    kv = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(kv)
+    kv._lib.emu_alloc.restype = ctypes.c_void_p
+    kv._lib.emu_alloc.argtypes = [ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
+    kv._lib.emu_free.argtypes = [ctypes.c_void_p]
+    return kv
+
+
+class Memory:
+    def __init__(self, kv, nbytes, device, at_end, skip=0):
+        self.kv, self.base = kv, kv._lib.emu_alloc(nbytes + skip, device, at_end)
+        self.ptr = self.base + skip
+        self.array = np.ctypeslib.as_array((ctypes.c_uint8 * nbytes).from_address(self.ptr))
+
+    def free(self):
+        self.kv._lib.emu_free(self.base)
+
+
+def one_case(kv, seed, bad_page=False):
+    rng = random.Random(seed)
+    layout, L, H, e = rng.choice([0, 1, 2]), rng.choice([1, 2, 3]), rng.choice([1, 2, 3, 5, 8]), rng.choice([1, 2])
+    D = rng.choice([8, 16, 24, 40, 64, 80, 96, 128, 256, 320])
+    D = 64 if D * e % 16 else D
+    R, P = H * D * e, rng.choice([1, 1, 2, 3, 5, 7, 16, 64, 100])
+    n = 1 if bad_page else rng.choice([1, 1, 2, 3, 5, 70])
+    most = max(1, 60000 // (L * 2 * R) // min(n, 5) * 2)
+    spans = []
+    for _ in range(n):
+        T = rng.randint(1 if bad_page else 0, most if n < 70 else max(1, most // 8))
+        cap = T + rng.choice([0, 0, 1, 3, 17])
+        spans.append((T, -(-cap // P) * P if layout == 1 else cap))
+    need = sum(-(-t // P) for t, _ in spans)
+    S = (need + rng.randint(1, 4)) * P
+    nr = np.random.default_rng(seed)
+    perm = nr.permutation(S // P).astype(np.int32)
+    l0 = rng.randint(0, L - 1)
+    l1 = rng.randint(l0 + 1, L)
+    at_end, keep = rng.randint(0, 1), []
+
+    def mem(nbytes, device, end=at_end, skip=0):
+        keep.append(Memory(kv, nbytes, device, end, skip))
+        return keep[-1]
+    img = nr.integers(0, 256, size=(2, L, S, R), dtype=np.uint8)
+    pool = [[mem(S * R, 1) for _ in range(L)] for _ in range(2)]
+    for k in range(2):
+        for l in range(L):
+            pool[k][l].array[:] = img[k, l].reshape(-1)
+    launch = kv.launch(rng.choice([0, 1, 2, 3]), rng.choice([0, 64, 128, 192]), rng.choice([0, 4, 8, 16]),
+                       rng.choice([0, 0, 0, kv.KVIO_LAUNCH_CACHED, kv.KVIO_LAUNCH_NO_LDS]))
+    staged = layout != 1 and rng.random() < 0.15 and not bad_page
+    if staged:
+        launch.flags |= kv.KVIO_LAUNCH_STAGED
+    h = kv.kvio_pool_create(L, H, D, e, P, S, [m.ptr for m in pool[0]], [m.ptr for m in pool[1]], launch, launch, layout,
+                            staging_bytes=8 * P * R * rng.choice([1, 2, 5]) if staged else 0)
+    work, at = [], 0
+    for T, cap in spans:
+        nbytes, count = max(16, oracle.host_chunk_bytes(LAYOUT[layout], L, cap, R, P)), -(-T // P)
+        src, dst = (mem(nbytes, 0, skip=16 * rng.randint(0, 20)) for _ in range(2))
+        src.array[:] = nr.integers(0, 256, nbytes, dtype=np.uint8)
+        dst.array[:] = 0x55
+        table = mem(max(16, -(-4 * count // 16) * 16), 1)
+        pages = perm[at:at + count].copy()
+        given = pages.copy()
+        if bad_page:
+            given[rng.randrange(count)] = rng.choice([-1, S // P, 2 ** 31 - 1, -2 ** 31])
+        table.array[:4 * count] = given.view(np.uint8)
+        work.append((T, cap, pages, given, src, dst, table))
+        at += count
+    kv.kvio_load(h, [(w[4].ptr, w[1], w[0], w[6].ptr) for w in work], l0, l1)
+    got = np.stack([np.stack([m.array.reshape(S, R) for m in row]) for row in pool])
+    exp = img.copy()
+    oracle.load_layout(exp[0], exp[1], P, [(w[4].array, w[1], w[0], w[2]) for w in work], LAYOUT[layout], num_heads=H,
+                       layer_begin=l0, layer_end=l1)
+    if bad_page:
+        for p in work[0][2][work[0][2] != work[0][3]]:
+            exp[:, :, p * P:(p + 1) * P] = img[:, :, p * P:(p + 1) * P]
+        with pytest.raises(kv.KvioError) as err:
+            kv.kvio_check(h)
+        assert err.value.status == kv.KVIO_ERANGE and f"context page {np.flatnonzero(work[0][2] != work[0][3])[0]}:" in err.value.detail
+    assert np.array_equal(got, exp), f"load of case {seed}"
+    kv.kvio_offload(h, [(w[5].ptr, w[1], w[0], w[6].ptr) for w in work], 0, L)
+    for T, cap, pages, given, _, dst, _ in work:
+        want = np.full(len(dst.array), 0x55, np.uint8)
+        oracle.offload_layout(exp[0], exp[1], P, [(want, cap, T, pages)], LAYOUT[layout], num_heads=H)
+        if bad_page:        # a chunk of fill bytes goes through the same pages: what the skipped one keeps
+            fill, marks = np.full_like(exp, 0x55), np.full_like(want, 0)
+            keep_pages = np.flatnonzero(pages == given)
+            mark = np.zeros_like(exp)
+            mark[:, :, (pages[keep_pages][:, None] * P + np.arange(P)).reshape(-1)] = 1
+            oracle.offload_layout(mark[0], mark[1], P, [(marks, cap, T, pages)], LAYOUT[layout], num_heads=H)
+            want[marks == 0] = 0x55
+            del fill
+        assert np.array_equal(dst.array, want), f"offload of case {seed}"
+    if not bad_page:
+        kv.kvio_check(h)
+    kv.kvio_pool_destroy(h)
+    for m in keep:
+        m.free()
+
+
+def run_cases(out, first, last, bad_page):
+    kv = load(out)
+    for seed in range(first, last):
+        print("case", seed, "bad page" if bad_page else "", flush=True)      # a fault ends the process: the last line names it
+        one_case(kv, seed, bad_page)
+
+
+@pytest.fixture(scope="module")
+def emulated(tmp_path_factory):
+    out = {}
+    for name, extra in (("whole", ()), ("split", ("-DKVIO_MAX_SPAN_VECS=40",))):
+        out[name] = str(tmp_path_factory.mktemp(name))
+        build(out[name], extra)
+    return out
+
+
+@pytest.mark.parametrize("name,first,last,bad_page", [("whole", 0, 260, False), ("whole", 260, 320, True),
+                                                      ("split", 320, 420, False), ("split", 420, 440, True)])
+def test_library_on_emulated_waves(emulated, name, first, last, bad_page):
+    """In a process of its own: an access out of bounds ends it."""
+    code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
+            f"import test_emulated_kernels as t\nt.run_cases({emulated[name]!r}, {first}, {last}, {bad_page})")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]
