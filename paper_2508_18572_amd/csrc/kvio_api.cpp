@@ -72,7 +72,8 @@ Shape resolve(const kvio_launch &l, const Shape &def) {
     s.tile_kib = l.tile_kib > 0 ? l.tile_kib : def.tile_kib;
     s.nontemporal = (l.flags & KVIO_LAUNCH_CACHED) == 0;
     s.grows = l.workgroups == 0;
-    s.device_scope = s.nontemporal && int64_t(s.workgroups) * (s.threads / 64) * s.tile_kib * 1024 >= kSc1MinInflight;
+    s.local = def.local;
+    s.device_scope = s.nontemporal && !s.local && int64_t(s.workgroups) * (s.threads / 64) * s.tile_kib * 1024 >= kSc1MinInflight;
     return s;
 }
 
@@ -91,7 +92,7 @@ kvio_status check_launch(const kvio_launch &l, const char *which) {
 // Device-visible address of [p, p + bytes), or an error if the device cannot
 // reach it or the allocation that holds it is shorter than `bytes`.
 kvio_status device_view(const void *p, uint64_t bytes, bool want_device_memory, const char *what,
-                        const uint8_t **out) {
+                        const uint8_t **out, int *device) {
     hipPointerAttribute_t attr;
     memset(&attr, 0, sizeof attr);
     hipError_t e = hipPointerGetAttributes(&attr, p);
@@ -130,6 +131,7 @@ kvio_status device_view(const void *p, uint64_t bytes, bool want_device_memory, 
                     "only %llu from there", what, p, (unsigned long long)bytes,
                     (unsigned long long)(dev >= b && static_cast<uint64_t>(dev - b) <= size ? size - (dev - b) : 0));
     *out = dev;
+    if (device != nullptr) *device = attr.type == hipMemoryTypeDevice ? attr.device : -1;
     return KVIO_OK;
 }
 
@@ -338,7 +340,7 @@ kvio_status validate_spans(const PoolGeom &g, const kvio_span *spans, int32_t n,
                         (long long)s.num_tokens, (long long)s.host_tokens);
         if (s.num_tokens > INT32_MAX)
             return fail(KVIO_EINVAL, "%s: span %d: num_tokens %lld >= 2^31", fn, i, (long long)s.num_tokens);
-        Resolved r{nullptr, s.page_idx, s.host_tokens, s.num_tokens};
+        Resolved r{nullptr, s.page_idx, s.host_tokens, s.num_tokens, -1};
         if (s.num_tokens > 0) {
             if (s.host == nullptr) return fail(KVIO_EINVAL, "%s: span %d: null host chunk", fn, i);
             if (s.page_idx == nullptr) return fail(KVIO_EINVAL, "%s: span %d: null page table", fn, i);
@@ -364,7 +366,7 @@ kvio_status validate_spans(const PoolGeom &g, const kvio_span *spans, int32_t n,
                 reach = (uint64_t(l1 - 1) * 2 + 1) * uint64_t(s.host_tokens) * uint64_t(R) +
                         uint64_t(s.num_tokens) * uint64_t(R);
             }
-            kvio_status st = device_view(s.host, reach, false, "host chunk", &r.host);
+            kvio_status st = device_view(s.host, reach, false, "host chunk", &r.host, &r.device);
             if (st != KVIO_OK) return st;
             const int64_t pages = (s.num_tokens + g.page_size - 1) / g.page_size;
             const uint8_t *pt = nullptr;
@@ -379,6 +381,10 @@ kvio_status validate_spans(const PoolGeom &g, const kvio_span *spans, int32_t n,
         out[i] = r;
     }
     return KVIO_OK;
+}
+
+bool all_local(const Resolved *rs, int32_t n, int device) {
+    return std::all_of(rs, rs + n, [&](const Resolved &r) { return r.num_tokens == 0 || r.device == device; });
 }
 
 // Fields of a launch that do not depend on its spans.
@@ -408,7 +414,7 @@ void cut_tiles(CopyArgs *a, const Shape &shape, Direction dir) {
     a->row_div = divider(V);
     a->vec_step_rows = static_cast<int32_t>(64 / V);
     a->vec_step_cols = static_cast<int32_t>(64 % V);
-    a->whole_rows = dir == kOffload && !shape.device_scope && a->host_layout != KVIO_HOST_HEAD_MAJOR;
+    a->whole_rows = dir == kOffload && !shape.device_scope && !shape.local && a->host_layout != KVIO_HOST_HEAD_MAJOR;
     if (a->whole_rows) {
         a->tile_vecs = static_cast<int32_t>(most);
         a->tile_rows = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(most / V, 1), 64));
@@ -528,7 +534,9 @@ kvio_status run_copy(kvio_pool_t p, const kvio_span *spans, int32_t n, int32_t l
                               resolve(lc, kvio::kDefaultStaged), fn);
         lc = kvio_launch{0, 0, 0, lc.flags & ~KVIO_LAUNCH_STAGED};   // small: the kernel path, default shape
     }
-    const kvio::Shape shape = resolve(lc, kvio::default_shape(dir, bytes, p->g.host_layout));
+    const kvio::Shape shape = resolve(lc, kvio::all_local(rs.data(), n, p->device)
+                                              ? kvio::kDefaultLocal
+                                              : kvio::default_shape(dir, bytes, p->g.host_layout));
     return kvio::launch_spans(p->g, p->d_layers, p->d_err, rs.data(), n, l0, l1, dir, shape, stream, fn);
 }
 

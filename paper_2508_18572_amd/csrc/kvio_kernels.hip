@@ -734,16 +734,18 @@ static void launch_layout(const CopyArgs &a, dim3 grid, dim3 block, hipStream_t 
     } else {
         const bool wide = a.vec_per_row % 64 == 0;
         if constexpr (DIR == kOffload && !SC1) {
-            if (wide)
-                hipLaunchKernelGGL((kvio_copy_kernel_paced<U, NT, true, HL>), grid, block, 0, stream, a);
-            else
-                hipLaunchKernelGGL((kvio_copy_kernel_paced<U, NT, false, HL>), grid, block, 0, stream, a);
-        } else {
-            if (wide)
-                hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, true, HL>), grid, block, 0, stream, a);
-            else
-                hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, false, HL>), grid, block, 0, stream, a);
+            if (a.whole_rows) {
+                if (wide)
+                    hipLaunchKernelGGL((kvio_copy_kernel_paced<U, NT, true, HL>), grid, block, 0, stream, a);
+                else
+                    hipLaunchKernelGGL((kvio_copy_kernel_paced<U, NT, false, HL>), grid, block, 0, stream, a);
+                return;
+            }
         }
+        if (wide)
+            hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, true, HL>), grid, block, 0, stream, a);
+        else
+            hipLaunchKernelGGL((kvio_copy_kernel<DIR, U, NT, SC1, false, HL>), grid, block, 0, stream, a);
     }
 }
 

@@ -40,6 +40,7 @@ struct Resolved {
     const int32_t *page_idx;
     int64_t host_tokens;
     int64_t num_tokens;
+    int device;                // the GPU whose memory holds the chunk, -1: host memory
 };
 
 // Check a pool description's sizes, layout and launch shapes (not its layer
@@ -53,6 +54,8 @@ kvio_status resolve_layers(const kvio_pool_desc *d, const PoolGeom &g, const cha
 // out[0 .. n).  Nothing is enqueued.
 kvio_status validate_spans(const PoolGeom &g, const kvio_span *spans, int32_t n, int32_t l0, int32_t l1,
                            const char *fn, Resolved *out);
+// Whether all of the chunks that take part lie in the memory of GPU `device`.
+bool all_local(const Resolved *rs, int32_t n, int device);
 // Validate a launch shape; fill in a shape from it and the defaults.
 kvio_status check_launch(const kvio_launch &l, const char *which);
 Shape resolve(const kvio_launch &l, const Shape &def);
@@ -62,7 +65,7 @@ inline int64_t planes(const PoolGeom &g, int64_t layers) {
 }
 // Device-visible address of [p, p + bytes) (see kvio_api.cpp).
 kvio_status device_view(const void *p, uint64_t bytes, bool want_device_memory, const char *what,
-                        const uint8_t **out);
+                        const uint8_t **out, int *device = nullptr);
 // Fields of a launch that do not depend on its spans.
 void common_args(const PoolGeom &g, uint8_t *const *layers, unsigned long long *err, const Shape &shape,
                  Direction dir, int32_t l0, CopyArgs *a);

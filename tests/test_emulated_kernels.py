@@ -93,7 +93,7 @@ def one_case(kv, seed, bad_page=False):
     perm = nr.permutation(S // P).astype(np.int32)
     l0 = rng.randint(0, L - 1)
     l1 = rng.randint(l0 + 1, L)
-    at_end, keep = rng.randint(0, 1), []
+    at_end, keep, local = rng.randint(0, 1), [], int(seed % 4 == 3)      # chunks in device memory
 
     def mem(nbytes, device, end=at_end, skip=0):
         keep.append(Memory(kv, nbytes, device, end, skip))
@@ -113,7 +113,7 @@ def one_case(kv, seed, bad_page=False):
     work, at = [], 0
     for T, cap in spans:
         nbytes, count = max(16, oracle.host_chunk_bytes(LAYOUT[layout], L, cap, R, P)), -(-T // P)
-        src, dst = (mem(nbytes, 0, skip=16 * rng.randint(0, 20)) for _ in range(2))
+        src, dst = (mem(nbytes, local, skip=16 * rng.randint(0, 20)) for _ in range(2))
         src.array[:] = nr.integers(0, 256, nbytes, dtype=np.uint8)
         dst.array[:] = 0x55
         table = mem(max(16, -(-4 * count // 16) * 16), 1)
