@@ -222,9 +222,10 @@ kvio_status kvio_load_layer(kvio_pool_t pool, const kvio_span *spans, int32_t n_
  * -- the table of layer addresses and the error word -- lives in a static
  * 4 KiB device array of the library (one per GPU, held until the process
  * ends), so the call takes at most KVIO_NOALLOC_MAX_LAYERS layers and at most
- * KVIO_MAX_SPANS_PER_LAUNCH spans (KVIO_EINVAL beyond either).  Each call
- * first enqueues a one-workgroup kernel that writes the layer table and
- * clears the error word, then the load kernel.  Every call on a GPU shares
+ * KVIO_MAX_SPANS_PER_LAUNCH spans (KVIO_EINVAL beyond either).  The layer
+ * table travels in the load kernel's arguments where it fits beside the spans
+ * (64 - ceil(L / 3) of them); with more spans the call first enqueues a
+ * one-workgroup kernel that writes it to the array.  Every call on a GPU shares
  * that array: calls that overlap on one GPU (on different streams, or from
  * different threads) race and must be ordered by the caller.  A page index
  * outside [0, S / P) is skipped, never dereferenced, and not reported (use a

@@ -474,11 +474,13 @@ hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream
 
 kvio_status launch_spans(const PoolGeom &g, uint8_t *const *layers, unsigned long long *err, const Resolved *rs,
                          int32_t n, int32_t l0, int32_t l1, Direction dir, const Shape &shape, hipStream_t stream,
-                         const char *fn) {
+                         const char *fn, uint8_t *const *own_table) {
     CopyArgs a;
     common_args(g, layers, err, shape, dir, l0, &a);
+    const int32_t most_spans = own_table != nullptr ? spans_beside_table(g.num_layers) : KVIO_MAX_SPANS_PER_LAUNCH;
     auto launch = [&]() -> kvio_status {
         if (a.n_spans == 0) return KVIO_OK;
+        if (own_table != nullptr) memcpy(a.spans + a.n_spans, own_table, 2 * size_t(g.num_layers) * sizeof *own_table);
         const hipError_t e = launch_capped(a, dir, shape, stream);
         a.n_spans = 0;
         return e == hipSuccess ? KVIO_OK : fail_hip(e, fn);
@@ -492,7 +494,7 @@ kvio_status launch_spans(const PoolGeom &g, uint8_t *const *layers, unsigned lon
         for (int32_t i = 0; i < n; ++i) {
             const Resolved &r = rs[i];
             for (int64_t t0 = 0; t0 < r.num_tokens; t0 += most_rows) {
-                if (a.n_spans == KVIO_MAX_SPANS_PER_LAUNCH) {
+                if (a.n_spans == most_spans) {
                     const kvio_status st = launch();
                     if (st != KVIO_OK) return st;
                 }

@@ -48,7 +48,10 @@ inline Divider divider(int64_t d) {
 // Tiles of narrow rows are cut where (host address / 16) & cut_mask is 0 (the
 // first tile of a plane is shorter by what precedes the plane's first vector).
 struct CopyArgs {
-    uint8_t *const *layers;        // device table: layers[kv * num_layers + l]
+    // Device table: layers[kv * num_layers + l].  Null: the table lies behind the
+    // last span, in the place of spans that the launch does not have (loads, and
+    // offloads that are not paced).
+    uint8_t *const *layers;
     unsigned long long *err;       // device error record (0 = none)
     int64_t row_bytes;             // bytes of a host row: R, or De for head-major chunks
     int64_t pitch;                 // bytes from one pool row to the next: R
@@ -84,6 +87,11 @@ struct CopyArgs {
     int32_t tile_prefix[KVIO_MAX_SPANS_PER_LAUNCH + 1];
     SpanArg spans[KVIO_MAX_SPANS_PER_LAUNCH];
 };
+
+// Spans a launch may hold beside a layer table of its own.
+inline int32_t spans_beside_table(int32_t num_layers) {
+    return KVIO_MAX_SPANS_PER_LAUNCH - static_cast<int32_t>((2 * int64_t(num_layers) * sizeof(uint8_t *) + sizeof(SpanArg) - 1) / sizeof(SpanArg));
+}
 
 // Most vectors of a span in one plane and most planes of a launch: what lies in
 // a plane is counted in 32 bits.  Larger transfers are split by the host (a

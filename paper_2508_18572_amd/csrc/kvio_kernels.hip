@@ -213,7 +213,10 @@ __device__ __forceinline__ Tile locate(Args &a, const TileCursor &c) {
     // The layer table is written before the launch and never during it, so it
     // is read through the scalar cache: a vector load would wait its turn
     // behind the compute unit's host reads.
-    KVIO_CONSTANT uint64_t *layers = reinterpret_cast<KVIO_CONSTANT uint64_t *>(reinterpret_cast<uintptr_t>(a.layers));
+    // Without one it lies in the arguments, behind the spans.
+    KVIO_CONSTANT uint64_t *layers = a.layers != nullptr
+        ? reinterpret_cast<KVIO_CONSTANT uint64_t *>(reinterpret_cast<uintptr_t>(a.layers))
+        : reinterpret_cast<KVIO_CONSTANT uint64_t *>(a.spans + a.n_spans);
     t.pool = reinterpret_cast<uint8_t *>(layers[(lkv & 1) * a.num_layers + (lkv >> 1)]) + head * a.row_bytes;
     uint8_t *base = const_cast<uint8_t *>(sp.host);
     int32_t v0 = (c.w - a.tile_prefix[c.span]) * a.tile_vecs;

@@ -75,10 +75,12 @@ hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream
 // Enqueue the kernel launches of a transfer of validated spans, one launch
 // per KVIO_MAX_SPANS_PER_LAUNCH spans; `layers` (device table of 2 * L layer
 // addresses) and `err` (device error word) are what the kernels read and
-// record into.  Launches with no rows are skipped.
+// record into.  Launches with no rows are skipped.  With `own_table` (2 * L
+// addresses in host memory, `layers` null) each launch carries the table in its
+// arguments and takes spans_beside_table(L) spans, which must be at least one.
 kvio_status launch_spans(const PoolGeom &g, uint8_t *const *layers, unsigned long long *err, const Resolved *rs,
                          int32_t n, int32_t l0, int32_t l1, Direction dir, const Shape &shape, hipStream_t stream,
-                         const char *fn);
+                         const char *fn, uint8_t *const *own_table = nullptr);
 // KVIO_LAUNCH_STAGED transfers (kvio_staged.cpp).
 kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvio_span *spans, int32_t n,
                        int32_t l0, int32_t l1, hipStream_t stream, Direction dir, const Shape &shape,

@@ -163,10 +163,57 @@ def run_cases(out, first, last, bad_page):
         one_case(kv, seed, bad_page)
 
 
+def noalloc_case(kv, L, n, layout, seed):
+    """The load that takes a description: every layer's table entry is used, with n
+    contexts of which the middle one is empty (the table lies behind the spans that
+    remain) and the last one longer than a split build's launch takes."""
+    H, D, e, P = 2, 16, 1, 3
+    R, nr = H * D * e, np.random.default_rng(seed)
+    tokens = [1 + (i * 5) % 7 for i in range(n)]
+    if n > 2:
+        tokens[n // 2] = 0
+    tokens[-1] = 45
+    caps = [-(-t // P) * P for t in tokens]
+    perm, at = nr.permutation(sum(caps) // P + 2).astype(np.int32), 0
+    S = len(perm) * P
+    img = nr.integers(0, 256, size=(2, L, S, R), dtype=np.uint8)
+    keep = [[Memory(kv, S * R, 1, seed & 1) for _ in range(L)] for _ in range(2)]
+    for k in range(2):
+        for l in range(L):
+            keep[k][l].array[:] = img[k, l].reshape(-1)
+    spans, ora, extra = [], [], []
+    for t, cap in zip(tokens, caps):
+        chunk, table = Memory(kv, max(16, L * 2 * cap * R), 0, seed & 1), Memory(kv, max(16, cap // P * 4), 1, 0)
+        chunk.array[:] = nr.integers(0, 256, len(chunk.array), dtype=np.uint8)
+        pages = perm[at:at + cap // P].copy()
+        at += cap // P
+        table.array[:4 * len(pages)] = pages.view(np.uint8)
+        spans.append((chunk.ptr, cap, t, table.ptr))
+        ora.append((chunk.array, cap, t, pages))
+        extra += [chunk, table]
+    desc, held = kv.pool_desc(L, H, D, e, P, S, [m.ptr for m in keep[0]], [m.ptr for m in keep[1]], host_layout=layout)
+    l0 = L // 3
+    kv.kvio_load_noalloc(desc, spans, l0, L)
+    got = np.stack([np.stack([m.array.reshape(S, R) for m in row]) for row in keep])
+    oracle.load_layout(img[0], img[1], P, ora, LAYOUT[layout], num_heads=H, layer_begin=l0, layer_end=L)
+    assert np.array_equal(got, img), f"noalloc load of {n} spans, {L} layers"
+    for m in keep[0] + keep[1] + extra:
+        m.free()
+
+
+def run_noalloc(out):
+    kv = load(out)
+    for L in (1, 2, 3, 4, 64, 127, 128):         # the most spans beside the table, and one more
+        beside = 64 - -(-L // 3)
+        for n in sorted({1, 2, beside - 1, beside, min(beside + 1, 64)}):
+            print("noalloc", L, n, flush=True)
+            noalloc_case(kv, L, n, (L + n) % 3, 1000 * L + n)
+
+
 @pytest.fixture(scope="module")
 def emulated(tmp_path_factory):
     out = {}
-    for name, extra in (("whole", ()), ("split", ("-DKVIO_MAX_SPAN_VECS=40",))):
+    for name, extra in (("whole", ()), ("split", ("-DKVIO_MAX_SPAN_VECS=40"))):
         out[name] = str(tmp_path_factory.mktemp(name))
         build(out[name], extra)
     return out
@@ -178,5 +225,13 @@ def test_library_on_emulated_waves(emulated, name, first, last, bad_page):
     """In a process of its own: an access out of bounds ends it."""
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
             f"import test_emulated_kernels as t\nt.run_cases({emulated[name]!r}, {first}, {last}, {bad_page})")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]
+
+
+@pytest.mark.parametrize("name", ["whole", "split"])
+def test_noalloc_table_in_the_arguments(emulated, name):
+    code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
+            f"import test_emulated_kernels as t\nt.run_noalloc({emulated[name]!r})")
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]
