@@ -12,13 +12,6 @@
 #include "kvio_internal.h"
 #include "kvio_pool.h"
 
-// Least bytes of a copy that is split off (a build may lower it to have small
-// calls split).
-#ifndef KVIO_STAGE_END_BYTES
-#define KVIO_STAGE_END_BYTES (int64_t(4) << 20)
-#endif
-constexpr int64_t kStageEndBytes = KVIO_STAGE_END_BYTES;
-
 namespace kvio {
 
 // Staged transfer (KVIO_LAUNCH_STAGED).  Work is packed into staging slots as
@@ -129,26 +122,14 @@ kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvi
         ++chunk;
         return KVIO_OK;
     };
-    // A load ends with the scatter of its last slot and an offload begins with
-    // the gather of its first, with the link idle meanwhile: a 256 MiB call, whose
-    // layers all fit one slot, has nothing to overlap at all.  So a few layers are
-    // split off there, as many as keep the link busy for as long as the rest takes
-    // in HBM (a 32nd; HBM is over 40 times as fast) and not below
-    // kStageEndBytes a copy, whose start costs some 10 us: a 256 MiB load 4872 -> 4796 us.
     int64_t layer_bytes = 0;                  // one layer of every span
     for (int32_t s = 0; s < n; ++s) layer_bytes += 2 * rs[size_t(s)].num_tokens * R;
     if (layer_bytes == 0) return KVIO_OK;
     auto plan = [&]() -> kvio_status {
-        bool split = false;
         for (int32_t l = l0; l < l1;) {
             if (layer_bytes <= cap) {
                 // whole spans over g layers per slot
-                int32_t g = int32_t(std::min<int64_t>(l1 - l, cap / layer_bytes));
-                const int64_t end = std::max<int64_t>((g + 31) / 32, (kStageEndBytes * n + layer_bytes - 1) / layer_bytes);
-                if (!split && end <= g / 2 && (dir == kvio::kLoad ? l + g == l1 : l == l0)) {
-                    g = int32_t(dir == kvio::kLoad ? g - end : end);
-                    split = true;
-                }
+                const int32_t g = int32_t(std::min<int64_t>(l1 - l, cap / layer_bytes));
                 for (int32_t s = 0; s < n; ++s) {
                     const int64_t T = rs[size_t(s)].num_tokens;
                     if (T == 0) continue;
