@@ -213,7 +213,7 @@ def run_noalloc(out):
 @pytest.fixture(scope="module")
 def emulated(tmp_path_factory):
     out = {}
-    for name, extra in (("whole", ()), ("split", ("-DKVIO_MAX_SPAN_VECS=40"))):
+    for name, extra in (("whole", ()), ("split", ("-DKVIO_MAX_SPAN_VECS=40",))):
         out[name] = str(tmp_path_factory.mktemp(name))
         build(out[name], extra)
     return out
