@@ -224,7 +224,7 @@ kvio_status kvio_load_layer(kvio_pool_t pool, const kvio_span *spans, int32_t n_
  * ends), so the call takes at most KVIO_NOALLOC_MAX_LAYERS layers and at most
  * KVIO_MAX_SPANS_PER_LAUNCH spans (KVIO_EINVAL beyond either).  The layer
  * table travels in the load kernel's arguments where it fits beside the spans
- * (64 - ceil(L / 3) of them); with more spans the call first enqueues a
+ * (64 - ceil(2 * L / 5) of them); with more spans the call first enqueues a
  * one-workgroup kernel that writes it to the array.  Every call on a GPU shares
  * that array: calls that overlap on one GPU (on different streams, or from
  * different threads) race and must be ordered by the caller.  A page index

@@ -88,7 +88,8 @@ struct CopyArgs {
     SpanArg spans[KVIO_MAX_SPANS_PER_LAUNCH];
 };
 
-// Spans a launch may hold beside a layer table of its own.
+// Spans a launch may hold beside a layer table of its own: 64 - ceil(2 L / 5).
+static_assert(sizeof(SpanArg) == 40, "kvio.h states how many spans go beside the layer table");
 inline int32_t spans_beside_table(int32_t num_layers) {
     return KVIO_MAX_SPANS_PER_LAUNCH - static_cast<int32_t>((2 * int64_t(num_layers) * sizeof(uint8_t *) + sizeof(SpanArg) - 1) / sizeof(SpanArg));
 }

@@ -103,9 +103,9 @@ extern "C" kvio_status kvio_load_noalloc(const kvio_pool_desc *desc, const kvio_
     const kvio::Shape shape = kvio::resolve(
         desc->load_launch,
         kvio::default_shape(kvio::kLoad, tokens * 2 * (layer_end - layer_begin) * g.row_bytes, g.host_layout));
-    // Kernel arguments hold 64 spans of 48 bytes whatever a call brings, so the
+    // Kernel arguments hold 64 spans of 40 bytes whatever a call brings, so the
     // table goes into the room of the spans it does not bring where it fits (one
-    // span: always; 64 layers: up to 42): one launch instead of two.  Nobody reads
+    // span: always; 64 layers: up to 38): one launch instead of two.  Nobody reads
     // the error word, so nothing need clear it.  A 32 KiB load: 8.3 -> 6.2 us.
     // Beyond that the table in memory stays: the spans would take several launches.
     if (n_spans <= kvio::spans_beside_table(g.num_layers))

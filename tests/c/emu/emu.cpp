@@ -168,8 +168,14 @@ uint64_t emu_ballot(bool v, const char *what) {
 
 void *emu_kernarg() { return kernarg; }
 
+namespace {
+int64_t launches = 0;
+}
+extern "C" int64_t emu_launches() { return launches; }
+
 void emu_launch(dim3 grid, dim3 block, const std::function<void()> &lane, const void *arg, size_t bytes) {
     if (block.x == 0 || block.x % kLanes != 0 || grid.x == 0) die("launch shape", "launch");
+    ++launches;
     if (w.stacks == nullptr) w.stacks = static_cast<char *>(malloc(kLanes * kStack));
     kernarg = emu_alloc(bytes, 1, 1);
     memcpy(kernarg, arg, bytes);

@@ -61,6 +61,7 @@ def load(out):
     kv._lib.emu_alloc.restype = ctypes.c_void_p
     kv._lib.emu_alloc.argtypes = [ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
     kv._lib.emu_free.argtypes = [ctypes.c_void_p]
+    kv._lib.emu_launches.restype = ctypes.c_int64
     return kv
 
 
@@ -163,7 +164,14 @@ def run_cases(out, first, last, bad_page):
         one_case(kv, seed, bad_page)
 
 
-def noalloc_case(kv, L, n, layout, seed):
+def beside_table(L):
+    """Spans beside the layer table in a launch's arguments, as include/kvio.h states it."""
+    header = open(os.path.join(ROOT, "include", "kvio.h")).read()
+    num, den = re.search(r"64 - ceil\((\d+) \* L / (\d+)\) of them", header).groups()
+    return 64 - -(-int(num) * L // int(den))
+
+
+def noalloc_case(kv, L, n, layout, seed, split):
     """The load that takes a description: every layer's table entry is used, with n
     contexts of which the middle one is empty (the table lies behind the spans that
     remain) and the last one longer than a split build's launch takes."""
@@ -192,22 +200,25 @@ def noalloc_case(kv, L, n, layout, seed):
         ora.append((chunk.array, cap, t, pages))
         extra += [chunk, table]
     desc, held = kv.pool_desc(L, H, D, e, P, S, [m.ptr for m in keep[0]], [m.ptr for m in keep[1]], host_layout=layout)
-    l0 = L // 3
+    l0, before = L // 3, kv._lib.emu_launches()
     kv.kvio_load_noalloc(desc, spans, l0, L)
+    launches = kv._lib.emu_launches() - before
     got = np.stack([np.stack([m.array.reshape(S, R) for m in row]) for row in keep])
     oracle.load_layout(img[0], img[1], P, ora, LAYOUT[layout], num_heads=H, layer_begin=l0, layer_end=L)
     assert np.array_equal(got, img), f"noalloc load of {n} spans, {L} layers"
+    if not split:       # the table in the one launch's arguments, or written by a kernel before it
+        assert launches == (1 if n <= beside_table(L) else 2), (L, n, launches)
     for m in keep[0] + keep[1] + extra:
         m.free()
 
 
-def run_noalloc(out):
+def run_noalloc(out, split):
     kv = load(out)
-    for L in (1, 2, 3, 4, 64, 127, 128):         # the most spans beside the table, and one more
-        beside = 64 - -(-L // 3)
+    for L in (1, 2, 3, 4, 5, 64, 80, 127, 128):  # the most spans beside the table, and one more
+        beside = beside_table(L)
         for n in sorted({1, 2, beside - 1, beside, min(beside + 1, 64)}):
             print("noalloc", L, n, flush=True)
-            noalloc_case(kv, L, n, (L + n) % 3, 1000 * L + n)
+            noalloc_case(kv, L, n, (L + n) % 3, 1000 * L + n, split)
 
 
 @pytest.fixture(scope="module")
@@ -232,6 +243,6 @@ def test_library_on_emulated_waves(emulated, name, first, last, bad_page):
 @pytest.mark.parametrize("name", ["whole", "split"])
 def test_noalloc_table_in_the_arguments(emulated, name):
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
-            f"import test_emulated_kernels as t\nt.run_noalloc({emulated[name]!r})")
+            f"import test_emulated_kernels as t\nt.run_noalloc({emulated[name]!r}, {name == 'split'})")
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]
