@@ -3,8 +3,10 @@ kvio_load with a pool handle, through the C ABI: two calls in a row, the
 second with a smaller input, on pools that start identical; both pools must
 be byte for byte equal after each call, and equal to the CPU oracle's load
 of the same host chunks.  Covers every host layout, a partial last page,
-several spans, a layer sub-range, the largest layer count the static table
-holds, and out-of-range page indices (skipped on both paths)."""
+several spans, a layer sub-range, the largest layer count, both places of the
+layer table (the kernel's arguments, or with more spans the static array, which
+a kernel of its own fills first), and out-of-range page indices (skipped on
+both paths)."""
 import numpy as np
 import pytest
 
@@ -99,8 +101,9 @@ def test_noalloc_load_matches_pool_handle_twice(kv, layout):
 
 
 def test_noalloc_largest_layer_count_and_skipped_pages(kv):
-    """128 layers (the static table's limit), then a smaller call whose first
-    span names an out-of-range page: both paths skip those rows; the handle
+    """128 layers (the most a call takes; with so few spans their table lies in
+    the kernel's arguments), then a smaller call whose first span names an
+    out-of-range page: both paths skip those rows; the handle
     path reports it, the no-alloc path moves the rest identically."""
     import torch
     L, H, D, P, S = kv.KVIO_NOALLOC_MAX_LAYERS, 8, 128, 4, 512      # R = 2 KiB: wide rows
@@ -204,3 +207,66 @@ def test_noalloc_load_replays_in_a_hip_graph(kv):
             torch.cuda.synchronize()
         del g
     del keep_desc
+
+
+@pytest.mark.parametrize("captured", [False, True], ids=["eager", "graph"])
+@pytest.mark.parametrize("n", [12, 13, 64])
+def test_noalloc_both_places_of_the_layer_table(kv, n, captured):
+    """128 layers leave room for 12 spans beside their table in the kernel's
+    arguments; beyond that a kernel writes the table to the static array and the
+    load behind it reads it there.  Two calls back to back on one stream, into
+    pools of their own: a table left over from the first would send the second
+    call's rows into the first pool.  Eager, and replayed from a graph with new
+    host bytes and eager work between replays."""
+    import torch
+    L, H, D, P = kv.KVIO_NOALLOC_MAX_LAYERS, 2, 16, 4               # R = 64 bytes
+    R, rng = H * D * 2, np.random.default_rng(n)
+    tokens = [1 + (7 * i) % 11 for i in range(n)]
+    caps = [-(-t // P) * P for t in tokens]
+    S = (sum(caps) // P + 3) * P
+    pools, imgs, descs, spans, oracles, keep = [], [], [], [], [], []
+    for which in range(2):
+        img = rng.integers(0, 256, size=(2, L, S, R), dtype=np.uint8)
+        pool = torch.from_numpy(img.view(np.uint16).reshape(2, L, S, H, D).copy()).cuda()
+        desc, held = kv.pool_desc(L, H, D, 2, P, S, [pool[0, l].data_ptr() for l in range(L)],
+                                  [pool[1, l].data_ptr() for l in range(L)])
+        perm, at, sp, ora = rng.permutation(S // P).astype(np.int32), 0, [], []
+        for t, cap in zip(tokens, caps):
+            hb, pages = kv.HostBuffer(L * 2 * cap * R), perm[at:at + cap // P].copy()
+            hb.array[:] = 0
+            at += cap // P
+            pt = torch.from_numpy(pages).cuda()
+            sp.append((hb.ptr, cap, t, pt.data_ptr()))
+            ora.append((hb.array, cap, t, pages))
+            keep += [hb, pt]
+        pools.append(pool), imgs.append(img), descs.append(desc), spans.append(sp), oracles.append(ora)
+        keep.append(held)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+
+    def calls():
+        for which in range(2):
+            kv.kvio_load_noalloc(descs[which], spans[which], 0, L, stream=s)
+    calls()                                                          # warm-up outside the capture
+    torch.cuda.synchronize()
+    if captured:
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            calls()
+    for rep in range(3):
+        print(f"[no_alloc] {n} spans, {'graph' if captured else 'eager'}, pass {rep}", flush=True)
+        for ora in oracles:
+            for array, _, _, _ in ora:
+                W.fill_np(array, int(rng.integers(1 << 30)), W.LLAMA8B)
+        g.replay() if captured else calls()
+        torch.cuda.synchronize()
+        for pool, img, ora in zip(pools, imgs, oracles):
+            oracle.load(img[0], img[1], P, ora)
+            assert np.array_equal(_bytes(pool), img), f"pass {rep}: pool differs from the oracle"
+            pool.view(torch.int16).add_(0)                           # eager work between passes
+        torch.cuda.synchronize()
+    if captured:
+        del g
+    for x in keep:
+        if hasattr(x, "free"):
+            x.free()
