@@ -96,12 +96,15 @@ inline int32_t spans_beside_table(int32_t num_layers) {
 
 // Most vectors of a span in one plane and most planes of a launch: what lies in
 // a plane is counted in 32 bits.  Larger transfers are split by the host (a
-// build may lower the first to have small ones split).
+// build may lower them to have small ones split).
 #ifndef KVIO_MAX_SPAN_VECS
 #define KVIO_MAX_SPAN_VECS (int64_t(1) << 30)
 #endif
+#ifndef KVIO_MAX_PLANES
+#define KVIO_MAX_PLANES (int64_t(1) << 30)
+#endif
 constexpr int64_t kMaxSpanVecs = KVIO_MAX_SPAN_VECS;
-constexpr int64_t kMaxPlanes = int64_t(1) << 30;
+constexpr int64_t kMaxPlanes = KVIO_MAX_PLANES;
 constexpr int64_t kMaxWaves = int64_t(1) << 20;
 
 enum Direction { kLoad = 0, kOffload = 1 };

@@ -128,8 +128,9 @@ kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvi
     auto plan = [&]() -> kvio_status {
         for (int32_t l = l0; l < l1;) {
             if (layer_bytes <= cap) {
-                // whole spans over g layers per slot
-                const int32_t g = int32_t(std::min<int64_t>(l1 - l, cap / layer_bytes));
+                // whole spans over g layers per slot (and no more planes than a launch counts)
+                const int64_t most_layers = std::max<int64_t>(kMaxPlanes / planes(p->g, 1), 1);
+                const int32_t g = int32_t(std::min({int64_t(l1 - l), cap / layer_bytes, most_layers}));
                 for (int32_t s = 0; s < n; ++s) {
                     const int64_t T = rs[size_t(s)].num_tokens;
                     if (T == 0) continue;

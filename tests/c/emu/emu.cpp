@@ -10,6 +10,8 @@
 
 #include <map>
 
+#include "kvio_internal.h"
+
 thread_local dim3 threadIdx, blockIdx, blockDim, gridDim;
 
 namespace {
@@ -176,6 +178,11 @@ extern "C" int64_t emu_launches() { return launches; }
 void emu_launch(dim3 grid, dim3 block, const std::function<void()> &lane, const void *arg, size_t bytes) {
     if (block.x == 0 || block.x % kLanes != 0 || grid.x == 0) die("launch shape", "launch");
     ++launches;
+    if (bytes == sizeof(kvio::CopyArgs)) {
+        const auto &a = *static_cast<const kvio::CopyArgs *>(arg);
+        const int64_t one_layer = a.host_layout == KVIO_HOST_HEAD_MAJOR ? 2 * a.num_heads : 2;
+        if (a.planes > kvio::kMaxPlanes && a.planes > one_layer) die("more planes than a launch counts", "launch");
+    }
     if (w.stacks == nullptr) w.stacks = static_cast<char *>(malloc(kLanes * kStack));
     kernarg = emu_alloc(bytes, 1, 1);
     memcpy(kernarg, arg, bytes);

@@ -3,7 +3,7 @@ the 64 lanes of a wave are coroutines that must meet at every cross-lane
 operation, values taken as wave-uniform must be, and every buffer lies against
 an inaccessible page), against the oracle: every form the entry points take --
 host layouts, row widths, page sizes, ragged and empty spans, chunks at every
-16-byte offset, spans longer than a plane's 32-bit count, out-of-range pages,
+16-byte offset, spans and layer ranges beyond a launch's 32-bit counts, out-of-range pages,
 launch shapes, staged transfers -- on kernels that count vectors rather than
 rows."""
 import ctypes
@@ -221,17 +221,52 @@ def run_noalloc(out, split):
             noalloc_case(kv, L, n, (L + n) % 3, 1000 * L + n, split)
 
 
+def run_staged_layers(out):
+    """Staged transfers whose slots hold more layers than a launch counts planes of
+    (4 in this build): the slot goes in several launches (the emulator refuses one
+    with more)."""
+    kv = load(out)
+    for layout, L, H in ((0, 5, 1), (2, 5, 1), (2, 7, 2), (0, 1, 3)):
+        D, e, P = 16, 1, 4
+        R, nr, before = H * D * e, np.random.default_rng(L), kv._lib.emu_launches()
+        img = nr.integers(0, 256, size=(2, L, 3 * P, R), dtype=np.uint8)
+        keep = [[Memory(kv, 3 * P * R, 1, 1) for _ in range(L)] for _ in range(2)]
+        for k in range(2):
+            for l in range(L):
+                keep[k][l].array[:] = img[k, l].reshape(-1)
+        mode = kv.launch(flags=kv.KVIO_LAUNCH_STAGED)
+        h = kv.kvio_pool_create(L, H, D, e, P, 3 * P, [m.ptr for m in keep[0]], [m.ptr for m in keep[1]], mode, mode,
+                                layout, staging_bytes=4 * L * 2 * P * R)
+        src, dst, table = Memory(kv, L * 2 * P * R, 0, 1), Memory(kv, L * 2 * P * R, 0, 1), Memory(kv, 16, 1, 1)
+        src.array[:] = nr.integers(0, 256, len(src.array), dtype=np.uint8)
+        dst.array[:] = 0x55
+        pages = np.array([2], np.int32)
+        table.array[:4] = pages.view(np.uint8)
+        kv.kvio_load(h, [(src.ptr, P, P, table.ptr)], 0, L)
+        kv.kvio_offload(h, [(dst.ptr, P, P, table.ptr)], 0, L)
+        kv.kvio_check(h)
+        oracle.load_layout(img[0], img[1], P, [(src.array, P, P, pages)], LAYOUT[layout], num_heads=H)
+        assert np.array_equal(np.stack([np.stack([m.array.reshape(3 * P, R) for m in row]) for row in keep]), img)
+        assert np.array_equal(src.array, dst.array)
+        print("staged layers", layout, L, H, kv._lib.emu_launches() - before, "launches", flush=True)
+        kv.kvio_pool_destroy(h)
+        for m in keep[0] + keep[1] + [src, dst, table]:
+            m.free()
+
+
 @pytest.fixture(scope="module")
 def emulated(tmp_path_factory):
     out = {}
-    for name, extra in (("whole", ()), ("split", ("-DKVIO_MAX_SPAN_VECS=40",))):
+    for name, extra in (("whole", ()), ("split", ("-DKVIO_MAX_SPAN_VECS=40",)),
+                        ("planes", ("-DKVIO_MAX_PLANES=4",))):
         out[name] = str(tmp_path_factory.mktemp(name))
         build(out[name], extra)
     return out
 
 
 @pytest.mark.parametrize("name,first,last,bad_page", [("whole", 0, 260, False), ("whole", 260, 320, True),
-                                                      ("split", 320, 420, False), ("split", 420, 440, True)])
+                                                      ("split", 320, 420, False), ("split", 420, 440, True),
+                                                      ("planes", 440, 480, False)])
 def test_library_on_emulated_waves(emulated, name, first, last, bad_page):
     """In a process of its own: an access out of bounds ends it."""
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
@@ -244,5 +279,12 @@ def test_library_on_emulated_waves(emulated, name, first, last, bad_page):
 def test_noalloc_table_in_the_arguments(emulated, name):
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
             f"import test_emulated_kernels as t\nt.run_noalloc({emulated[name]!r}, {name == 'split'})")
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]
+
+
+def test_staged_slot_of_many_layers(emulated):
+    code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
+            f"import test_emulated_kernels as t\nt.run_staged_layers({emulated['planes']!r})")
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]
