@@ -82,7 +82,7 @@ def parse():
     ap.add_argument("--noncoherent-host", action="store_true", help="coarse-grained pinned host chunks")
     ap.add_argument("--host-layout", choices=["token", "page", "head"], default="token",
                     help="host chunk layout: token-major (default), page-first, or head-major")
-    ap.add_argument("--no-lds", action="store_true", help="set KVIO_LAUNCH_NO_LDS (accepted, without effect)")
+    ap.add_argument("--no-lds", action="store_true", help="set KVIO_LAUNCH_NO_LDS (head-major chunks of segments below 64 bytes go by address)")
     ap.add_argument("--staged", action="store_true",
                     help="copy engine through an HBM staging buffer + scatter/gather kernel (KVIO_LAUNCH_STAGED)")
     ap.add_argument("--staging-mib", type=int, default=0, help="staging per direction (4 slots); 0 = default")

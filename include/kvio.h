@@ -95,7 +95,8 @@ typedef enum kvio_status {
  *                          (((l*2 + kv)*H + h)*host_tokens + t) * De;
  *                          De must be a multiple of 16.  Converting it to
  *                          the token-major pool is a head/token transpose
- *                          done by address. */
+ *                          done by address, of segments below 64 bytes
+ *                          through LDS. */
 #define KVIO_HOST_TOKEN_MAJOR 0
 #define KVIO_HOST_PAGE_FIRST 1
 #define KVIO_HOST_HEAD_MAJOR 2
@@ -104,7 +105,8 @@ typedef enum kvio_status {
  * kernel on few compute units; cache bypass limits pollution).  Zero fields
  * take the library defaults.  Results never depend on these. */
 #define KVIO_LAUNCH_CACHED 0x1     /* plain loads/stores instead of non-temporal ones */
-#define KVIO_LAUNCH_NO_LDS 0x2     /* accepted, without effect: no kernel uses LDS */
+#define KVIO_LAUNCH_NO_LDS 0x2     /* head-major chunks of segments below 64 bytes: by address, not through LDS
+                                      (the others never use LDS) */
 /* KVIO_LAUNCH_STAGED (token-major and head-major chunks): instead of
  * wavefronts reading (writing) the pinned chunk across the host link, the
  * copy engine moves the chunk's contiguous runs to (from) an HBM staging buffer

@@ -73,8 +73,13 @@ Shape resolve(const kvio_launch &l, const Shape &def) {
     s.nontemporal = (l.flags & KVIO_LAUNCH_CACHED) == 0;
     s.grows = l.workgroups == 0;
     s.local = def.local;
+    s.lds = (l.flags & KVIO_LAUNCH_NO_LDS) == 0;
     s.device_scope = s.nontemporal && !s.local && int64_t(s.workgroups) * (s.threads / 64) * s.tile_kib * 1024 >= kSc1MinInflight;
     return s;
+}
+
+Shape default_shape(const PoolGeom &g, const kvio_launch &l, Direction dir, int64_t bytes) {
+    return default_shape(dir, bytes, g.host_layout, (l.flags & KVIO_LAUNCH_NO_LDS) == 0, g.num_heads, g.seg_bytes);
 }
 
 kvio_status check_launch(const kvio_launch &l, const char *which) {
@@ -403,8 +408,8 @@ void common_args(const PoolGeom &g, uint8_t *const *layers, unsigned long long *
     a->page_div = divider(g.page_size);
     a->host_layout = g.host_layout;
     a->num_heads = g.num_heads;
-    a->head_div = divider(g.num_heads);
     cut_tiles(a, shape, dir);
+    a->head_div = divider(a->transpose ? g.row_bytes / 16 : g.num_heads);
 }
 
 // Fill in the cut of the vectors of a plane into tiles.
@@ -414,10 +419,12 @@ void cut_tiles(CopyArgs *a, const Shape &shape, Direction dir) {
     a->row_div = divider(V);
     a->vec_step_rows = static_cast<int32_t>(64 / V);
     a->vec_step_cols = static_cast<int32_t>(64 % V);
+    a->transpose = transposes(a->host_layout, shape.lds, a->num_heads, a->row_bytes, shape.tile_kib);
     a->whole_rows = dir == kOffload && !shape.device_scope && !shape.local && a->host_layout != KVIO_HOST_HEAD_MAJOR;
-    if (a->whole_rows) {
+    if (a->whole_rows || a->transpose) {
         a->tile_vecs = static_cast<int32_t>(most);
-        a->tile_rows = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(most / V, 1), 64));
+        a->tile_rows = static_cast<int32_t>(
+            std::min<int64_t>(std::max<int64_t>(a->transpose ? most * 16 / a->pitch : most / V, 1), 64));
         return;
     }
     int64_t unit = 1;                        // cuts lie at multiples of this many vectors
@@ -443,7 +450,7 @@ void add_span(CopyArgs *a) {
     int64_t before = a->cut_mask;            // planes that begin at differing places: the most
     if (s.host_tokens * a->row_bytes % 256 == 0)
         before = static_cast<int64_t>((reinterpret_cast<uintptr_t>(s.host) >> 4) & uintptr_t(a->cut_mask));
-    const int64_t tiles = a->whole_rows
+    const int64_t tiles = a->whole_rows || a->transpose
                               ? (int64_t(s.num_tokens) + a->tile_rows - 1) / a->tile_rows
                               : (int64_t(s.num_tokens) * a->vec_per_row + before + a->tile_vecs - 1) / a->tile_vecs;
     if (a->n_spans == 0) a->tile_prefix[0] = 0;
@@ -462,7 +469,7 @@ hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream
     const int64_t waves_per_wg = s.threads / 64;
     if (s.grows) {
         int64_t vecs = 0;                    // of the tile_vecs * plane_tiles a plane's tiles could hold
-        for (int32_t i = 0; i < a.n_spans; ++i) vecs += int64_t(a.spans[i].num_tokens) * a.vec_per_row;
+        for (int32_t i = 0; i < a.n_spans; ++i) vecs += int64_t(a.spans[i].num_tokens) * a.vec_per_row * (a.transpose ? a.num_heads : 1);
         const int64_t room = int64_t(a.plane_tiles) * a.tile_vecs / vecs;
         s.workgroups *= static_cast<int>(std::max<int64_t>(1, std::min(room, kMostGrowth)));
     }
@@ -487,10 +494,10 @@ kvio_status launch_spans(const PoolGeom &g, uint8_t *const *layers, unsigned lon
     };
     // Spans and layer ranges beyond what a launch counts in 32 bits go in pieces.
     const int64_t most_rows = std::max<int64_t>(kMaxSpanVecs / a.vec_per_row, 1);
-    const int64_t most_layers = std::max<int64_t>(kMaxPlanes / planes(g, 1), 1);
+    const int64_t most_layers = std::max<int64_t>(kMaxPlanes / planes(a, 1), 1);
     for (int64_t l = l0; l < l1; l += most_layers) {
         a.layer_begin = static_cast<int32_t>(l);
-        a.planes = static_cast<int32_t>(planes(g, std::min(l + most_layers, int64_t(l1)) - l));
+        a.planes = static_cast<int32_t>(planes(a, std::min(l + most_layers, int64_t(l1)) - l));
         for (int32_t i = 0; i < n; ++i) {
             const Resolved &r = rs[i];
             for (int64_t t0 = 0; t0 < r.num_tokens; t0 += most_rows) {
@@ -536,9 +543,8 @@ kvio_status run_copy(kvio_pool_t p, const kvio_span *spans, int32_t n, int32_t l
                               resolve(lc, kvio::kDefaultStaged), fn);
         lc = kvio_launch{0, 0, 0, lc.flags & ~KVIO_LAUNCH_STAGED};   // small: the kernel path, default shape
     }
-    const kvio::Shape shape = resolve(lc, kvio::all_local(rs.data(), n, p->device)
-                                              ? kvio::kDefaultLocal
-                                              : kvio::default_shape(dir, bytes, p->g.host_layout));
+    const kvio::Shape shape = resolve(lc, kvio::all_local(rs.data(), n, p->device) ? kvio::kDefaultLocal
+                                                                                   : default_shape(p->g, lc, dir, bytes));
     return kvio::launch_spans(p->g, p->d_layers, p->d_err, rs.data(), n, l0, l1, dir, shape, stream, fn);
 }
 

@@ -39,7 +39,8 @@ inline Divider divider(int64_t d) {
 // between calls on different streams.
 //
 // Work decomposition: a "plane" is one run of host rows of the launch's layer
-// range -- a (layer, K|V), or for head-major chunks a (layer, K|V, head) --
+// range -- a (layer, K|V), or for head-major chunks a (layer, K|V, head) unless
+// the launch transposes --
 // planes ordered layer-major; a "tile" is tile_vecs consecutive 16-byte vectors
 // of one span in one plane.  tile_prefix[s] is the first tile of span s inside
 // a plane, so a plane holds plane_tiles = tile_prefix[n_spans] tiles and the
@@ -65,7 +66,7 @@ struct CopyArgs {
     int32_t vec_per_row;           // V = row_bytes / 16
     Divider page_div;              // by P
     Divider row_div;               // by V
-    Divider head_div;              // by num_heads
+    Divider head_div;              // by num_heads; where a launch transposes, by num_heads * V
     Divider plane_div;             // by plane_tiles
     int32_t vec_step_rows;         // 64 / V: rows a lane's vector index advances per 64 vectors
     int32_t vec_step_cols;         // 64 % V: and columns (carried into the row at V)
@@ -77,6 +78,7 @@ struct CopyArgs {
     int32_t n_spans;               // spans in this launch, 1 .. KVIO_MAX_SPANS_PER_LAUNCH
     int32_t host_layout;           // KVIO_HOST_*
     int32_t num_heads;             // H (head-major chunks)
+    int32_t transpose;             // head-major: tiles are tile_rows whole rows of all heads
     // Set by launch_copy: waves of a workgroup and of the launch, and the vectors,
     // rows and columns from a wave's tile to its next one.
     int32_t waves_per_wg;
@@ -118,6 +120,7 @@ struct Shape {
     bool device_scope;  // offload host stores with the device-scope (SC1) policy
     bool grows;         // the grid is the library's: it may grow for short spans
     bool local;         // the chunks lie in the memory of the pool's own GPU
+    bool lds;           // head-major chunks: may transpose through LDS
 };
 
 // Library defaults for the launch shape, chosen by measurement on MI355X
@@ -139,25 +142,46 @@ struct Shape {
 // Where spans are so short that their tiles are mostly empty, a default grid
 // grows until as many bytes are in flight, up to kMostGrowth times.
 constexpr int kDefaultThreads = 256;
-constexpr Shape kDefaultLoad = {16, 192, 4, true, false, false, false};
-constexpr Shape kDefaultLoadMiddle = {24, 128, 4, true, false, false, false};
-constexpr Shape kDefaultLoadSmall = {32, 128, 4, true, false, false, false};
+constexpr Shape kDefaultLoad = {16, 192, 4, true, false, false, false, true};
+constexpr Shape kDefaultLoadMiddle = {24, 128, 4, true, false, false, false, true};
+constexpr Shape kDefaultLoadSmall = {32, 128, 4, true, false, false, false, true};
 constexpr int64_t kMiddleLoadBytes = int64_t(32) << 20;
 constexpr int64_t kSmallLoadBytes = int64_t(2) << 20;
-constexpr Shape kDefaultOffload = {32, kDefaultThreads, 16, true, false, false, false};
-constexpr Shape kDefaultOffloadPageFirst = {64, kDefaultThreads, 8, true, false, false, false};
+constexpr Shape kDefaultOffload = {32, kDefaultThreads, 16, true, false, false, false, true};
+constexpr Shape kDefaultOffloadPageFirst = {64, kDefaultThreads, 8, true, false, false, false, true};
 constexpr int64_t kMostGrowth = 8;
+// Head-major chunks whose segments are narrower than this many 16-byte vectors go
+// through LDS.  By address (a tile is one head's run of up to 64 rows) a step of
+// 16-byte segments holds 1 KiB, and its pool accesses are 16 bytes each; through
+// LDS a tile holds whole rows of all heads, and host runs and pool rows are both
+// long.  64 MiB, by address and through LDS, GB/s:
+//   loads     8 heads of 16 bytes 30.0, 57.3; 32 of 32 54.3, 57.2; 16 of 48 54.0, 50.1
+//   offloads  8 heads of 16 bytes 56.0, 56.5; 32 of 32 53.8, 56.3; 16 of 48 53.6, 54.2
+//   2 MiB     8 of 16: load 28.4, 50.7, offload 53.0, 50.3; 16 of 48: 49.7, 45.1, 50.5, 46.1
+//   quota of 8 x 256, 4 KiB steps: load 8 of 16 19.6, 42.6, offload 24.8, 43.4
+//   chunks in device memory: load 8 of 16 392, 2640, offload 1115, 2650
+// At 64 bytes the direct path leads (loads 57.2 against 56.7).  Loads take 32 waves
+// of 8 KiB steps at every size: 48 are 5% slower, 4 KiB steps 45% (the host runs of
+// a tile are its step divided by the heads).
+constexpr int kTransposeBelow = 4;
+constexpr Shape kDefaultLoadTranspose = {16, 128, 8, true, false, false, false, true};
+inline bool transposes(int host_layout, bool lds, int num_heads, int64_t seg_bytes, int tile_kib) {
+    return host_layout == KVIO_HOST_HEAD_MAJOR && lds && seg_bytes < kTransposeBelow * 16 && num_heads > 1 &&
+           num_heads * seg_bytes <= int64_t(tile_kib) * 1024;
+}
 // Chunks in the memory of the pool's own GPU (a copy between two caches, a gather
 // for a consumer there): nothing crosses the host link, so the whole chip copies,
 // with the compiler's stores.  256 MiB of 2 KiB rows in 90-93 us each way (5.9 TB/s
 // read and written) where the shapes and stores for host memory took 2039 and 587;
 // 256 to 2048 workgroups and steps of 4 to 16 KiB differ by 5%.
-constexpr Shape kDefaultLocal = {1024, kDefaultThreads, 4, true, false, false, true};
+constexpr Shape kDefaultLocal = {1024, kDefaultThreads, 4, true, false, false, true, true};
 
 // The default shape of a call that moves `bytes` in direction `dir` between
-// the pool and host chunks of layout `host_layout` (KVIO_HOST_*).
-inline Shape default_shape(int dir, int64_t bytes, int host_layout) {
+// the pool and host chunks of layout `host_layout` (KVIO_HOST_*), head-major ones
+// with `num_heads` segments of `seg_bytes`.
+inline Shape default_shape(int dir, int64_t bytes, int host_layout, bool lds, int num_heads, int64_t seg_bytes) {
     if (dir != 0) return host_layout == KVIO_HOST_PAGE_FIRST ? kDefaultOffloadPageFirst : kDefaultOffload;
+    if (transposes(host_layout, lds, num_heads, seg_bytes, kDefaultLoadTranspose.tile_kib)) return kDefaultLoadTranspose;
     return bytes < kSmallLoadBytes ? kDefaultLoadSmall : bytes < kMiddleLoadBytes ? kDefaultLoadMiddle : kDefaultLoad;
 }
 // Offloads whose quota keeps at least this many bytes in flight (waves x step)
@@ -175,7 +199,7 @@ constexpr int64_t kSc1MinInflight = KVIO_SC1_MIN_INFLIGHT;
 // Staged transfers: the scatter / gather between the HBM staging buffer and
 // the pool is HBM-bound, so it takes the whole chip (4 GiB of 2 KiB rows at
 // page size 1 in 1.75 ms, 2.4 TB/s of payload).
-constexpr Shape kDefaultStaged = {1024, kDefaultThreads, 16, true, false, false, true};
+constexpr Shape kDefaultStaged = {1024, kDefaultThreads, 16, true, false, false, true, true};
 
 // Fill in how the vectors of a plane are cut into tiles, from row_bytes and
 // host_layout: tiles of up to tile_kib KiB that touch at most 64 rows (a lane

@@ -195,6 +195,18 @@ struct Tile {
     int32_t end;
 };
 
+// The pool array of plane lkv = layer * 2 + K|V.
+// The layer table is written before the launch and never during it, so it
+// is read through the scalar cache: a vector load would wait its turn
+// behind the compute unit's host reads.
+// Without one it lies in the arguments, behind the spans.
+__device__ __forceinline__ uint8_t *pool_layer(Args &a, int32_t lkv) {
+    KVIO_CONSTANT uint64_t *layers = a.layers != nullptr
+        ? reinterpret_cast<KVIO_CONSTANT uint64_t *>(reinterpret_cast<uintptr_t>(a.layers))
+        : reinterpret_cast<KVIO_CONSTANT uint64_t *>(a.spans + a.n_spans);
+    return reinterpret_cast<uint8_t *>(layers[(lkv & 1) * a.num_layers + (lkv >> 1)]);
+}
+
 template <int HL, bool WIDE>
 __device__ __forceinline__ Tile locate(Args &a, const TileCursor &c) {
     Tile t;
@@ -210,14 +222,7 @@ __device__ __forceinline__ Tile locate(Args &a, const TileCursor &c) {
     t.rows = sp.num_tokens;
     t.token0 = sp.token0;
     t.plane = lkv;
-    // The layer table is written before the launch and never during it, so it
-    // is read through the scalar cache: a vector load would wait its turn
-    // behind the compute unit's host reads.
-    // Without one it lies in the arguments, behind the spans.
-    KVIO_CONSTANT uint64_t *layers = a.layers != nullptr
-        ? reinterpret_cast<KVIO_CONSTANT uint64_t *>(reinterpret_cast<uintptr_t>(a.layers))
-        : reinterpret_cast<KVIO_CONSTANT uint64_t *>(a.spans + a.n_spans);
-    t.pool = reinterpret_cast<uint8_t *>(layers[(lkv & 1) * a.num_layers + (lkv >> 1)]) + head * a.row_bytes;
+    t.pool = pool_layer(a, lkv) + head * a.row_bytes;
     uint8_t *base = const_cast<uint8_t *>(sp.host);
     int32_t v0 = (c.w - a.tile_prefix[c.span]) * a.tile_vecs;
     if constexpr (HL != kHostPageFirst) {
@@ -590,9 +595,9 @@ __global__ void __launch_bounds__((needs_narrow_bound<DIR, U, WIDE, HL>() ? kNar
 // pool rows lie R apart and start at the head's column.  So the head/token
 // transpose of the layout conversion is the same address arithmetic as the
 // paging, host accesses are whole runs whatever H, and nothing passes through
-// LDS.  Against a transpose through LDS whose tiles held all heads of a few
-// rows (host runs of 4 KiB / H), 64 MiB loads went from 35-57 to 56.6-57.2 GB/s over
-// 1 to 32 heads.
+// LDS.  Against the transpose through LDS (below; host runs of 4 KiB / H), 64 MiB
+// loads of segments of 64 bytes or more went from 35-57 to 56.6-57.2 GB/s over 1 to
+// 32 heads.
 template <int DIR, int U, bool NT, bool SC1>
 __global__ void __launch_bounds__(kNarrowBound) kvio_head_major_kernel(const CopyArgs) {
     copy_tiles<DIR, U, NT, SC1, false, kHostHeadMajor>(kernel_args());
@@ -616,6 +621,21 @@ __global__ void __launch_bounds__(kNarrowBound) kvio_head_major_kernel(const Cop
 // 0 6.87 / 8.99, 2 7.08 / 8.52, 4 7.38 / 7.96, 6 7.65 / 7.69, 8 7.95 / 7.96.
 constexpr int kPace = 6;
 
+// To the wave's next tile, if there is one.
+__device__ __forceinline__ bool cursor_next(Args &a, TileCursor &cur) {
+    int32_t from = cur.span;
+    cur.w += a.waves;
+    if (cur.w >= a.plane_tiles) {
+        const int32_t planes = static_cast<int32_t>(div_small(static_cast<uint32_t>(cur.w), a.plane_div));
+        cur.plane += planes;
+        cur.w -= planes * a.plane_tiles;
+        from = 0;
+    }
+    if (cur.plane >= a.planes) return false;
+    if (from == 0 || cur.w >= cur.end) cursor_to(a, cur, from);
+    return true;
+}
+
 struct RowTile {
     int span, layer, kv;
     int t0, nrows;                           // first row in the span, and rows
@@ -632,13 +652,19 @@ __device__ __forceinline__ RowTile row_tile(Args &a, const TileCursor &c) {
     return t;
 }
 
-// Lane r < nrows: pool slot of the tile's row r, or -1 (see lane_slot).
-__device__ __forceinline__ int row_slot(Args &a, Span &sp, const RowTile &t, int lane) {
+// Lane r: the pool page of the tile's row r (read only), of its last row where
+// there is none, so that the load carries no mask.
+__device__ __forceinline__ int32_t row_page(Args &a, Span &sp, const RowTile &t, int lane) {
+    const int r = lane < t.nrows ? lane : t.nrows - 1;
+    return sp.page_idx[div_small(static_cast<uint32_t>(sp.token0 + t.t0 + r), a.page_div)];
+}
+
+// And its pool slot, or -1 (see lane_slot).
+__device__ __forceinline__ int row_slot(Args &a, Span &sp, const RowTile &t, int lane, int32_t page) {
     int slot = -1;
     if (lane < t.nrows) {
         const uint32_t token = static_cast<uint32_t>(sp.token0 + t.t0 + lane);
         const uint32_t cpage = div_small(token, a.page_div);
-        const int32_t page = sp.page_idx[cpage];
         if (page >= 0 && page < a.num_pages) {
             slot = static_cast<int>(static_cast<uint32_t>(page) * static_cast<uint32_t>(a.page_size) +
                                     (token - cpage * static_cast<uint32_t>(a.page_size)));
@@ -665,7 +691,7 @@ __global__ void __launch_bounds__((HL != KVIO_HOST_TOKEN_MAJOR ? 256 : 1024)) kv
         const RowTile t = row_tile(a, cur);
         Span &sp = a.spans[t.span];
         const uint8_t *pool = a.layers[t.kv * a.num_layers + t.layer];
-        const int slot = row_slot(a, sp, t, lane);
+        const int slot = row_slot(a, sp, t, lane, row_page(a, sp, t, lane));
         uint8_t *host = const_cast<uint8_t *>(sp.host);
         const int64_t plane = static_cast<int64_t>(t.layer) * 2 + t.kv;
         int64_t hoff = 0;                    // page-first: lane r's row r from the chunk
@@ -717,23 +743,128 @@ __global__ void __launch_bounds__((HL != KVIO_HOST_TOKEN_MAJOR ? 256 : 1024)) kv
             }
         }
         __builtin_amdgcn_s_sleep(kPace);
-        int32_t from = cur.span;
-        cur.w += a.waves;
-        if (cur.w >= a.plane_tiles) {
-            const int32_t planes = static_cast<int32_t>(div_small(static_cast<uint32_t>(cur.w), a.plane_div));
-            cur.plane += planes;
-            cur.w -= planes * a.plane_tiles;
-            from = 0;
+        if (!cursor_next(a, cur)) return;
+    }
+}
+
+// ----------------------------------------------------------------------------
+// Head-major chunks of narrow segments (kTransposeBelow), through LDS.  A wave
+// owns a tile of n whole rows that fits its U KiB of LDS.  It reads the tile in
+// host order (per head, n * De contiguous bytes), writes each vector to its
+// place in pool order in its slice, and reads the slice back in pool order, so
+// both sides are runs: host reads of n * De bytes, pool writes of whole rows.
+// Offloads run the same two phases the other way round.  With Vd = De / 16:
+//   pool order  p = (r * H + h) * Vd + c     (row r, head h, vector c)
+//   host order  q = (h * n + r) * Vd + c
+// A tile's page-table entries are read a tile ahead, as in copy_tiles.
+// ----------------------------------------------------------------------------
+template <int DIR, int U, bool NT, bool SC1>
+__global__ void __launch_bounds__(kNarrowBound) kvio_head_transpose_kernel(const CopyArgs) {
+    HIP_DYNAMIC_SHARED(u32x4, lds)           // U * 64 vectors per wave
+    Args &a = kernel_args();
+    const int lane = threadIdx.x & 63;
+    const int wave_in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t g = static_cast<int32_t>(blockIdx.x) * a.waves_per_wg + wave_in_wg;
+    if (g >= a.total_tiles) return;
+    u32x4 *slice = lds + wave_in_wg * (U * 64);
+    const int Vd = a.vec_per_row, V = a.num_heads * Vd;
+    // The wave's lanes exchange data through its slice: what was written is there.
+    auto exchange = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    TileCursor cur = cursor_at(a, g);
+    RowTile t = row_tile(a, cur), next = t;
+    int32_t page = row_page(a, a.spans[t.span], t, lane);
+    asm volatile("" : : : "memory");         // ahead of the tile's reads
+    bool more = true;
+    auto look_ahead = [&] {
+        asm volatile("" : "+v"(page) : : "memory");      // done with it
+        more = cursor_next(a, cur);
+        if (more) next = row_tile(a, cur);
+        page = row_page(a, a.spans[next.span], next, lane);
+        asm volatile("" : : : "memory");
+    };
+#pragma unroll 1
+    for (;; t = next) {
+        Span &sp = a.spans[t.span];
+        const int32_t lkv = t.layer * 2 + t.kv;
+        uint8_t *pool = pool_layer(a, lkv);
+        const int n = t.nrows, nvec = n * V;
+        const int64_t head_stride = sp.host_tokens * a.row_bytes;
+        // Head 0's run at the tile's first row.
+        uint8_t *host = const_cast<uint8_t *>(sp.host) + static_cast<int64_t>(lkv) * a.num_heads * head_stride + t.t0 * a.row_bytes;
+        // Vector q of the tile in host order: its place in pool order, its row and
+        // its byte offset from `host`.
+        struct Host { int pool, r; int64_t off; };
+        auto host_order = [&](int q) -> Host {
+            const int hr = static_cast<int>(div_small(static_cast<uint32_t>(q), a.row_div));
+            const int h = static_cast<int>(static_cast<unsigned>(hr) / static_cast<unsigned>(n)), r = hr - h * n, c = q - hr * Vd;
+            return {r * V + h * Vd + c, r, h * head_stride + static_cast<int64_t>(r * Vd + c) * 16};
+        };
+        u32x4 buf[U];
+        if constexpr (DIR == kLoad) {
+            int pos[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int q = k * 64 + lane;
+                const Host x = host_order(q);
+                pos[k] = q < nvec ? x.pool : -1;
+                buf[k] = load16<NT>(q < nvec ? host + x.off : pool);
+            }
+            const int slot = row_slot(a, sp, t, lane, page);
+            look_ahead();
+#pragma unroll
+            for (int k = 0; k < U; ++k) arrive(buf[k]);
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (pos[k] >= 0) slice[pos[k]] = buf[k];
+            exchange();
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int p = k * 64 + lane;
+                const int r = static_cast<int>(div_small(static_cast<uint32_t>(p), a.head_div));
+                const int s = __shfl(slot, r & 63);
+                if (p < nvec && s >= 0) store16<NT>(pool + s * a.pitch + (p - r * V) * 16, slice[p]);
+            }
+        } else {
+            const int slot = row_slot(a, sp, t, lane, page);
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int p = k * 64 + lane;
+                const int r = static_cast<int>(div_small(static_cast<uint32_t>(p), a.head_div));
+                const int s = __shfl(slot, r & 63);
+                buf[k] = load16<NT>(pool + (p < nvec && s >= 0 ? s * a.pitch + (p - r * V) * 16 : 0));
+            }
+            look_ahead();
+#pragma unroll
+            for (int k = 0; k < U; ++k) arrive(buf[k]);
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (k * 64 + lane < nvec) slice[k * 64 + lane] = buf[k];
+            exchange();
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int q = k * 64 + lane;
+                const Host x = host_order(q);
+                const int s = __shfl(slot, x.r & 63);
+                if (q < nvec && s >= 0) store_host16<NT, SC1>(host + x.off, slice[x.pool]);
+            }
         }
-        if (cur.plane >= a.planes) return;
-        if (from == 0 || cur.w >= cur.end) cursor_to(a, cur, from);
+        exchange();                          // the next tile takes the slice
+        if (!more) return;
     }
 }
 
 template <int DIR, int U, bool NT, bool SC1, int HL>
 static void launch_layout(const CopyArgs &a, dim3 grid, dim3 block, hipStream_t stream) {
     if constexpr (HL == kHostHeadMajor) {
-        hipLaunchKernelGGL((kvio_head_major_kernel<DIR, U, NT, SC1>), grid, block, 0, stream, a);
+        if (a.transpose)
+            hipLaunchKernelGGL((kvio_head_transpose_kernel<DIR, U, NT, SC1>), grid, block,
+                               static_cast<size_t>(block.x / 64) * U * 1024, stream, a);
+        else
+            hipLaunchKernelGGL((kvio_head_major_kernel<DIR, U, NT, SC1>), grid, block, 0, stream, a);
     } else {
         const bool wide = a.vec_per_row % 64 == 0;
         if constexpr (DIR == kOffload && !SC1) {

@@ -102,7 +102,7 @@ extern "C" kvio_status kvio_load_noalloc(const kvio_pool_desc *desc, const kvio_
     init.err = reinterpret_cast<unsigned long long *>(base);
     const kvio::Shape shape = kvio::resolve(
         desc->load_launch,
-        kvio::default_shape(kvio::kLoad, tokens * 2 * (layer_end - layer_begin) * g.row_bytes, g.host_layout));
+        kvio::default_shape(g, desc->load_launch, kvio::kLoad, tokens * 2 * (layer_end - layer_begin) * g.row_bytes));
     // Kernel arguments hold 64 spans of 40 bytes whatever a call brings, so the
     // table goes into the room of the spans it does not bring where it fits (one
     // span: always; 64 layers: up to 38): one launch instead of two.  Nobody reads

@@ -59,9 +59,10 @@ bool all_local(const Resolved *rs, int32_t n, int device);
 // Validate a launch shape; fill in a shape from it and the defaults.
 kvio_status check_launch(const kvio_launch &l, const char *which);
 Shape resolve(const kvio_launch &l, const Shape &def);
-// Planes of `layers` layers of a pool.
-inline int64_t planes(const PoolGeom &g, int64_t layers) {
-    return layers * 2 * (g.host_layout == KVIO_HOST_HEAD_MAJOR ? g.num_heads : 1);
+Shape default_shape(const PoolGeom &g, const kvio_launch &l, Direction dir, int64_t bytes);
+// Planes of `layers` layers in a launch.
+inline int64_t planes(const CopyArgs &a, int64_t layers) {
+    return layers * 2 * (a.host_layout == KVIO_HOST_HEAD_MAJOR && !a.transpose ? a.num_heads : 1);
 }
 // Device-visible address of [p, p + bytes) (see kvio_api.cpp).
 kvio_status device_view(const void *p, uint64_t bytes, bool want_device_memory, const char *what,

@@ -42,6 +42,8 @@ kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvi
     const int64_t cap = std::min(p->slot_bytes, kMaxSpanVecs * 32);
     if (p->stage[dir] == nullptr) return fail(KVIO_EINVAL, "%s: the pool has no staging buffer for this direction", fn);
     hipStream_t ks = p->side_stream[dir];
+    CopyArgs cut;
+    common_args(p, shape, dir, l0, &cut);
     struct Unit { int32_t span; int64_t t0, n, off; };
     std::vector<Unit> units;
     units.reserve(KVIO_MAX_SPANS_PER_LAUNCH);
@@ -93,7 +95,7 @@ kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvi
         if (err != hipSuccess) return fail_hip(err, fn);
         kvio::CopyArgs a;
         common_args(p, shape, dir, lb, &a);
-        a.planes = static_cast<int32_t>(planes(p->g, g));
+        a.planes = static_cast<int32_t>(planes(a, g));
         for (const Unit &u : units) {
             SpanArg &sp = a.spans[a.n_spans];
             sp.host = reinterpret_cast<const uint8_t *>(reinterpret_cast<uintptr_t>(slot) + uintptr_t(u.off) -
@@ -129,7 +131,7 @@ kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvi
         for (int32_t l = l0; l < l1;) {
             if (layer_bytes <= cap) {
                 // whole spans over g layers per slot (and no more planes than a launch counts)
-                const int64_t most_layers = std::max<int64_t>(kMaxPlanes / planes(p->g, 1), 1);
+                const int64_t most_layers = std::max<int64_t>(kMaxPlanes / planes(cut, 1), 1);
                 const int32_t g = int32_t(std::min({int64_t(l1 - l), cap / layer_bytes, most_layers}));
                 for (int32_t s = 0; s < n; ++s) {
                     const int64_t T = rs[size_t(s)].num_tokens;

@@ -101,7 +101,7 @@ struct Wave {
     unsigned first_thread = 0;
 };
 Wave w;
-void *kernarg = nullptr;
+void *kernarg = nullptr, *shared = nullptr;
 
 void enter() {
     (*w.body)();
@@ -169,23 +169,28 @@ uint64_t emu_ballot(bool v, const char *what) {
 }
 
 void *emu_kernarg() { return kernarg; }
+void *emu_lds() { return shared; }
 
 namespace {
-int64_t launches = 0;
+int64_t launches = 0, last_tiles = 0;
 }
 extern "C" int64_t emu_launches() { return launches; }
+extern "C" int64_t emu_last_tiles() { return last_tiles; }    // of the last copy kernel
 
-void emu_launch(dim3 grid, dim3 block, const std::function<void()> &lane, const void *arg, size_t bytes) {
+void emu_launch(dim3 grid, dim3 block, size_t lds, const std::function<void()> &lane, const void *arg, size_t bytes) {
     if (block.x == 0 || block.x % kLanes != 0 || grid.x == 0) die("launch shape", "launch");
     ++launches;
     if (bytes == sizeof(kvio::CopyArgs)) {
         const auto &a = *static_cast<const kvio::CopyArgs *>(arg);
-        const int64_t one_layer = a.host_layout == KVIO_HOST_HEAD_MAJOR ? 2 * a.num_heads : 2;
+        const int64_t one_layer = a.host_layout == KVIO_HOST_HEAD_MAJOR && !a.transpose ? 2 * a.num_heads : 2;
+        last_tiles = a.total_tiles;
         if (a.planes > kvio::kMaxPlanes && a.planes > one_layer) die("more planes than a launch counts", "launch");
     }
     if (w.stacks == nullptr) w.stacks = static_cast<char *>(malloc(kLanes * kStack));
     kernarg = emu_alloc(bytes, 1, 1);
     memcpy(kernarg, arg, bytes);
+    if (lds > 64 << 10) die("too much LDS", "launch");
+    shared = lds ? emu_alloc(lds, 1, 1) : nullptr;
     gridDim = grid;
     blockDim = block;
     w.body = &lane;
@@ -197,5 +202,6 @@ void emu_launch(dim3 grid, dim3 block, const std::function<void()> &lane, const 
             run_wave();
         }
     emu_free(kernarg);
-    kernarg = nullptr;
+    if (shared) emu_free(shared);
+    kernarg = shared = nullptr;
 }

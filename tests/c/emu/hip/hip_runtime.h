@@ -23,6 +23,8 @@
 #define __launch_bounds__(...)
 #define __align__(n) __attribute__((aligned(n)))
 #define HIP_SYMBOL(x) (x)
+#define HIP_DYNAMIC_SHARED(type, name) type *name = static_cast<type *>(emu_lds());
+#define __builtin_amdgcn_fence(...) ((void)0)
 
 struct dim3 {
     unsigned x, y, z;
@@ -83,23 +85,25 @@ template <class T>
 hipError_t hipGetSymbolAddress(void **p, T &sym) { *p = (void *)&sym; return hipSuccess; }
 
 // ---------------------------------------------------------------- the device
-void emu_launch(dim3 grid, dim3 block, const std::function<void()> &lane, const void *arg, size_t bytes);
+void emu_launch(dim3 grid, dim3 block, size_t lds, const std::function<void()> &lane, const void *arg, size_t bytes);
 uint64_t emu_exchange(uint64_t v, int from, const char *what);   // `from` < 0: every lane must bring the same
 uint64_t emu_ballot(bool v, const char *what);
 void *emu_kernarg();
+void *emu_lds();
 
 template <class First, class... Rest>
-void emu_run(void (*k)(First, Rest...), dim3 grid, dim3 block, const First &first, const Rest &...rest) {
-    emu_launch(grid, block, [&] { k(first, rest...); }, &first, sizeof first);
+void emu_run(void (*k)(First, Rest...), dim3 grid, dim3 block, size_t lds, const First &first, const Rest &...rest) {
+    emu_launch(grid, block, lds, [&] { k(first, rest...); }, &first, sizeof first);
 }
 #define hipLaunchKernelGGL(k, grid, block, lds, stream, ...) \
-    emu_run(k, grid, block, __VA_ARGS__)
+    emu_run(k, grid, block, lds, __VA_ARGS__)
 
 inline int __shfl(int v, int lane) { return (int)emu_exchange((uint32_t)v, lane & 63, "shfl"); }
 inline long long __shfl(long long v, int lane) { return (long long)emu_exchange((uint64_t)v, lane & 63, "shfl64"); }
 inline uint32_t __builtin_amdgcn_readlane(uint32_t v, int lane) { return (uint32_t)emu_exchange(v, lane & 63, "readlane"); }
 inline uint32_t __builtin_amdgcn_readfirstlane(uint32_t v) { return (uint32_t)emu_exchange(v, -1, "readfirstlane"); }
 inline uint64_t __ballot(bool v) { return emu_ballot(v, "ballot"); }
+inline void __builtin_amdgcn_wave_barrier() { emu_ballot(true, "wave_barrier"); }
 inline bool __any(bool v) { return emu_ballot(v, "any") != 0; }
 inline bool __all(bool v) { return emu_ballot(v, "all") == ~uint64_t(0); }
 inline void __builtin_amdgcn_s_sleep(int) {}

@@ -61,7 +61,7 @@ def load(out):
     kv._lib.emu_alloc.restype = ctypes.c_void_p
     kv._lib.emu_alloc.argtypes = [ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
     kv._lib.emu_free.argtypes = [ctypes.c_void_p]
-    kv._lib.emu_launches.restype = ctypes.c_int64
+    kv._lib.emu_launches.restype = kv._lib.emu_last_tiles.restype = ctypes.c_int64
     return kv
 
 
@@ -254,6 +254,32 @@ def run_staged_layers(out):
             m.free()
 
 
+def run_full_steps(out):
+    """Narrow head segments: a wave's step is as full as 64 rows of all heads can make
+    it (a quarter may be lost to the tile's unit), in both directions."""
+    kv = load(out)
+    for De, H, kib in ((16, 8, 4), (16, 8, 16), (16, 3, 4), (32, 8, 4), (32, 4, 16), (48, 5, 4), (48, 5, 16)):
+        L, P, T = 2, 16, 512
+        R, nr = H * De, np.random.default_rng(De)
+        keep = [[Memory(kv, T * R, 1, 1) for _ in range(L)] for _ in range(2)]
+        mode = kv.launch(2, 64, kib)
+        h = kv.kvio_pool_create(L, H, De, 1, P, T, [m.ptr for m in keep[0]], [m.ptr for m in keep[1]], mode, mode, 2)
+        src, dst, table = Memory(kv, L * 2 * T * R, 0, 1), Memory(kv, L * 2 * T * R, 0, 1), Memory(kv, T // P * 4, 1, 1)
+        src.array[:] = nr.integers(0, 256, len(src.array), dtype=np.uint8)
+        pages = nr.permutation(T // P).astype(np.int32)
+        table.array[:] = pages.view(np.uint8)
+        step = min(kib * 1024, 64 * R)
+        kv.kvio_load(h, [(src.ptr, T, T, table.ptr)], 0, L)
+        load_tiles = kv._lib.emu_last_tiles()
+        kv.kvio_offload(h, [(dst.ptr, T, T, table.ptr)], 0, L)
+        assert np.array_equal(src.array, dst.array)
+        for tiles in (load_tiles, kv._lib.emu_last_tiles()):
+            assert tiles * step * 3 // 4 <= L * 2 * T * R, (De, H, kib, tiles)
+        kv.kvio_pool_destroy(h)
+        for m in keep[0] + keep[1] + [src, dst, table]:
+            m.free()
+
+
 @pytest.fixture(scope="module")
 def emulated(tmp_path_factory):
     out = {}
@@ -283,8 +309,9 @@ def test_noalloc_table_in_the_arguments(emulated, name):
     assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]
 
 
-def test_staged_slot_of_many_layers(emulated):
+@pytest.mark.parametrize("name,run", [("planes", "run_staged_layers"), ("whole", "run_full_steps")])
+def test_launch_limits_and_steps(emulated, name, run):
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
-            f"import test_emulated_kernels as t\nt.run_staged_layers({emulated['planes']!r})")
+            f"import test_emulated_kernels as t\nt.{run}({emulated[name]!r})")
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]

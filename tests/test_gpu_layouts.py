@@ -100,6 +100,17 @@ def test_head_major_parity(kv, L, H, D, P, S, spans, lds):
     run_layout_case(kv, 2, L, H, D, P, S, spans, launch=launch, seed=L * 5 + P + lds)
 
 
+@pytest.mark.parametrize("tile", [0, 4, 8, 16])
+@pytest.mark.parametrize("H,De", [(2, 16), (8, 16), (64, 16), (4, 32), (32, 32), (5, 48), (16, 48), (128, 48), (300, 16),
+                                  (8, 64)])
+def test_head_major_narrow_segments(kv, H, De, tile):
+    """Segments below 64 bytes go through LDS in tiles of whole rows, up to 64 of
+    them: rows that fit a step once, a few times and not at all (then by address),
+    contexts of less than a tile, of whole tiles and with a remainder, an empty one."""
+    spans = [(64, 64), (1, 3), (0, 2), (129, 144), (200, 200)]
+    run_layout_case(kv, 2, 2, H, De // 2, 5, 500, spans, l0=0, l1=2, launch=kv.launch(3 if tile else 0, 0, tile), seed=H + De)
+
+
 @pytest.mark.parametrize("wg,threads,tile", [(1, 64, 4), (5, 1024, 16), (64, 256, 8)])
 @pytest.mark.parametrize("layout", [1, 2])
 def test_layout_launch_shapes_and_subrange(kv, layout, wg, threads, tile):
