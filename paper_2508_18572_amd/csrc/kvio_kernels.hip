@@ -886,10 +886,11 @@ static void launch_layout(const CopyArgs &a, dim3 grid, dim3 block, hipStream_t 
 template <int DIR, int U, bool NT, bool SC1>
 static hipError_t launch_u(CopyArgs &a, const Shape &s, hipStream_t stream) {
     dim3 grid(s.workgroups), block(s.threads);
-    const bool wide = a.vec_per_row % 64 == 0;
+    // The bound goes by the step asked for, also where a smaller one serves (small
+    // tiles of narrow rows).  2 x 1024 threads with 16 KiB steps would otherwise read
+    // the link from two compute units, at 21 GB/s (rows of 112 bytes; 56.2 folded).
     const bool narrow_bound = a.host_layout != KVIO_HOST_TOKEN_MAJOR ||
-                              (wide ? needs_narrow_bound<DIR, U, true, kHostTokenMajor>()
-                                    : needs_narrow_bound<DIR, U, false, kHostTokenMajor>());
+                              (DIR == kLoad && s.tile_kib == 16 && a.vec_per_row % 64 != 0);
     if (narrow_bound && s.threads > kNarrowBound) {
         grid = dim3(static_cast<unsigned>(int64_t(s.workgroups) * s.threads / kNarrowBound));
         block = dim3(kNarrowBound);

@@ -61,7 +61,7 @@ def load(out):
     kv._lib.emu_alloc.restype = ctypes.c_void_p
     kv._lib.emu_alloc.argtypes = [ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
     kv._lib.emu_free.argtypes = [ctypes.c_void_p]
-    kv._lib.emu_launches.restype = kv._lib.emu_last_tiles.restype = ctypes.c_int64
+    kv._lib.emu_launches.restype = kv._lib.emu_last_tiles.restype = kv._lib.emu_last_block.restype = ctypes.c_int64
     return kv
 
 
@@ -255,15 +255,18 @@ def run_staged_layers(out):
 
 
 def run_full_steps(out):
-    """Narrow head segments: a wave's step is as full as 64 rows of all heads can make
-    it (a quarter may be lost to the tile's unit), in both directions."""
+    """Narrow rows and head segments: a wave's step is as full as 64 rows (of all heads)
+    can make it (a quarter may be lost to the tile's unit), in both directions, and
+    loads of narrow rows with 16 KiB steps keep the workgroups of 256 threads that
+    1024 are folded into, also where a smaller step would serve."""
     kv = load(out)
-    for De, H, kib in ((16, 8, 4), (16, 8, 16), (16, 3, 4), (32, 8, 4), (32, 4, 16), (48, 5, 4), (48, 5, 16)):
+    for De, H, kib, layout in ((16, 8, 4, 2), (16, 8, 16, 2), (16, 3, 4, 2), (32, 8, 4, 2), (32, 4, 16, 2), (48, 5, 4, 2), (48, 5, 16, 2),
+                               (48, 1, 4, 0), (48, 1, 4, 1), (112, 1, 16, 0), (112, 1, 16, 1), (80, 1, 16, 0), (96, 1, 8, 1)):
         L, P, T = 2, 16, 512
         R, nr = H * De, np.random.default_rng(De)
         keep = [[Memory(kv, T * R, 1, 1) for _ in range(L)] for _ in range(2)]
-        mode = kv.launch(2, 64, kib)
-        h = kv.kvio_pool_create(L, H, De, 1, P, T, [m.ptr for m in keep[0]], [m.ptr for m in keep[1]], mode, mode, 2)
+        mode = kv.launch(2, 1024 if kib == 16 else 64, kib)
+        h = kv.kvio_pool_create(L, H, De, 1, P, T, [m.ptr for m in keep[0]], [m.ptr for m in keep[1]], mode, mode, layout)
         src, dst, table = Memory(kv, L * 2 * T * R, 0, 1), Memory(kv, L * 2 * T * R, 0, 1), Memory(kv, T // P * 4, 1, 1)
         src.array[:] = nr.integers(0, 256, len(src.array), dtype=np.uint8)
         pages = nr.permutation(T // P).astype(np.int32)
@@ -271,6 +274,7 @@ def run_full_steps(out):
         step = min(kib * 1024, 64 * R)
         kv.kvio_load(h, [(src.ptr, T, T, table.ptr)], 0, L)
         load_tiles = kv._lib.emu_last_tiles()
+        assert kv._lib.emu_last_block() <= 256, (De, H, kib)
         kv.kvio_offload(h, [(dst.ptr, T, T, table.ptr)], 0, L)
         assert np.array_equal(src.array, dst.array)
         for tiles in (load_tiles, kv._lib.emu_last_tiles()):
