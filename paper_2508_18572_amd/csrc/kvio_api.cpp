@@ -475,7 +475,8 @@ hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream
         int64_t vecs = 0;                    // of the tile_vecs * plane_tiles a plane's tiles could hold
         for (int32_t i = 0; i < a.n_spans; ++i) vecs += int64_t(a.spans[i].num_tokens) * a.vec_per_row * (a.transpose ? a.num_heads : 1);
         const int64_t room = int64_t(a.plane_tiles) * a.tile_vecs / vecs;
-        s.workgroups *= static_cast<int>(std::max<int64_t>(1, std::min(room, kMostGrowth)));
+        const int64_t step = dir == kLoad ? std::max<int64_t>(int64_t(s.tile_kib) * 64, a.tile_vecs) : a.tile_vecs;
+        s.workgroups = static_cast<int>(std::min(s.workgroups * std::max<int64_t>(room, 1) * step / a.tile_vecs, s.workgroups * kMostGrowth));
     }
     // No more waves than tiles, and than the kernels count (far more than the chip holds).
     const int64_t max_wgs = (std::min(a.total_tiles, kMaxWaves) + waves_per_wg - 1) / waves_per_wg;

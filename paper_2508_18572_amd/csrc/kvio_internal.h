@@ -124,29 +124,34 @@ struct Shape {
 };
 
 // Library defaults for the launch shape, chosen by measurement on MI355X
-// (PCIe Gen5 x16 host link), on 16 of the 256 CUs for large loads.
-//   Load of 32 MiB or more: 16 workgroups x 3 waves, 4 KiB steps (192 KiB in
-//   flight).  That saturates the link (57.4 GB/s, the contiguous memcpy peak,
-//   at every row size; 128 KiB in flight reach 57.0), and more reads in flight
-//   slow what runs beside them: with 256 KiB a load and a background offload
-//   move 88 GB/s together, with 192 KiB 92.
-//   Loads of 2 MiB up to that: the same waves, 24 x 2: two on a CU wait less for
-//   one another's reads than three (2 MiB of 512-byte rows 40.2 against 40.4 us).
-//   Loads below 2 MiB: 32 x 2 waves, so that their few tiles take fewer rounds
-//   (256 KiB are 64 tiles of 4 KiB: 8.1 against 8.5 us; at 2 MiB a launch behind
-//   another takes 40.6 us with 64 waves and 40.0 with 48).
+// (PCIe Gen5 x16 host link), on 13 of the 256 CUs for large loads.
+//   Load of 32 MiB or more: 13 workgroups x 3 waves, 4 KiB steps (156 KiB in
+//   flight): 57.3 GB/s, where 48 waves reach 57.5.  More reads in flight slow what
+//   runs beside them: a 1M-token load beside a background offload moves 98.4 GB/s
+//   both ways with 39 waves, 96.7 with 42, 95.7 with 45, 95.0 with 48, of which the
+//   load 52.5, 50.7, 49.8, 49.4.
+//   Loads below that: 64 waves, 16 x 4 below 4 MiB and 32 x 2 above.  48 waves take
+//   as long alone (2 MiB of 512-byte rows 40.1 against 40.4 us), but on two streams,
+//   each with contexts of its own, 1.5 to 3% longer at every size (8 MiB: 155 against
+//   151 us).  Four waves on a CU lead two on small loads (256 KiB 8.3 against 8.6 us,
+//   on two streams 6.5 against 7.2) and are 0.5% behind from 8 MiB on; page-first,
+//   whose waves also work out row offsets, 2% behind from 1 MiB on.
 //   Offload: 32 workgroups x 4 waves with 16 KiB steps (57.0 GB/s with the
 //   device-scope host stores).  Page-first offloads take 64 x 4 waves with 8 KiB
 //   steps: 56.6-57.1 GB/s against 56.0-57.0 with 128 waves of 16 KiB (the same
 //   2 MiB in flight), ahead at every row width (2-4 GiB, page sizes 1 and 16).
-// Where spans are so short that their tiles are mostly empty, a default grid
-// grows until as many bytes are in flight, up to kMostGrowth times.
+// A default grid grows until as many bytes are in flight where tiles are mostly
+// empty, because spans are short, up to kMostGrowth times (64 head-major contexts of 1 to 7
+// tokens, rows of 512 bytes: 2.4 times faster than without, token-major 1.2; no
+// effect on a background offload beside: 91.4 against 91.3 GB/s both ways), and for
+// loads where rows are too narrow to fill a step (a tile's 64 rows of 16 bytes are 1 KiB).
 constexpr int kDefaultThreads = 256;
-constexpr Shape kDefaultLoad = {16, 192, 4, true, false, false, false, true};
-constexpr Shape kDefaultLoadMiddle = {24, 128, 4, true, false, false, false, true};
-constexpr Shape kDefaultLoadSmall = {32, 128, 4, true, false, false, false, true};
+constexpr Shape kDefaultLoad = {13, 192, 4, true, false, false, false, true};
+constexpr Shape kDefaultLoadMiddle = {32, 128, 4, true, false, false, false, true};
+constexpr Shape kDefaultLoadSmall = {16, kDefaultThreads, 4, true, false, false, false, true};
 constexpr int64_t kMiddleLoadBytes = int64_t(32) << 20;
-constexpr int64_t kSmallLoadBytes = int64_t(2) << 20;
+constexpr int64_t kSmallLoadBytes = int64_t(4) << 20;
+constexpr int64_t kSmallLoadBytesPageFirst = int64_t(512) << 10;
 constexpr Shape kDefaultOffload = {32, kDefaultThreads, 16, true, false, false, false, true};
 constexpr Shape kDefaultOffloadPageFirst = {64, kDefaultThreads, 8, true, false, false, false, true};
 constexpr int64_t kMostGrowth = 8;
@@ -182,7 +187,8 @@ constexpr Shape kDefaultLocal = {1024, kDefaultThreads, 4, true, false, false, t
 inline Shape default_shape(int dir, int64_t bytes, int host_layout, bool lds, int num_heads, int64_t seg_bytes) {
     if (dir != 0) return host_layout == KVIO_HOST_PAGE_FIRST ? kDefaultOffloadPageFirst : kDefaultOffload;
     if (transposes(host_layout, lds, num_heads, seg_bytes, kDefaultLoadTranspose.tile_kib)) return kDefaultLoadTranspose;
-    return bytes < kSmallLoadBytes ? kDefaultLoadSmall : bytes < kMiddleLoadBytes ? kDefaultLoadMiddle : kDefaultLoad;
+    const int64_t small = host_layout == KVIO_HOST_PAGE_FIRST ? kSmallLoadBytesPageFirst : kSmallLoadBytes;
+    return bytes < small ? kDefaultLoadSmall : bytes < kMiddleLoadBytes ? kDefaultLoadMiddle : kDefaultLoad;
 }
 // Offloads whose quota keeps at least this many bytes in flight (waves x step)
 // store into host memory with the SC1 policy: enough to cover the longer

@@ -62,6 +62,8 @@ def load(out):
     kv._lib.emu_alloc.argtypes = [ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
     kv._lib.emu_free.argtypes = [ctypes.c_void_p]
     kv._lib.emu_launches.restype = kv._lib.emu_last_tiles.restype = kv._lib.emu_last_block.restype = ctypes.c_int64
+    kv._lib.emu_last_waves.restype = kv._lib.emu_default_load_kib.restype = ctypes.c_int64
+    kv._lib.emu_default_load_kib.argtypes = [ctypes.c_int64, ctypes.c_int]
     return kv
 
 
@@ -284,6 +286,34 @@ def run_full_steps(out):
             m.free()
 
 
+def run_default_loads(out):
+    """Default loads below 32 MiB keep 256 KiB in flight (two of them on two streams
+    fill the link together), larger ones at most 156 (more slows an offload beside
+    them), and rows too narrow to fill a step take as many waves more."""
+    kv = load(out)
+    for layout in range(3):
+        for shift in range(15, 25):
+            assert kv._lib.emu_default_load_kib(1 << shift, layout) == 256, (layout, shift)
+        for shift in range(25, 36):
+            assert 128 < kv._lib.emu_default_load_kib(1 << shift, layout) <= 156, (layout, shift)
+    L, P = 1, 16
+    for R, T, waves in ((16, 16384, 256), (32, 8192, 128), (48, 8192, 85), (512, 512, 64)):
+        keep = [[Memory(kv, T * R, 1, 1) for _ in range(L)] for _ in range(2)]
+        h = kv.kvio_pool_create(L, 1, R, 1, P, T, [m.ptr for m in keep[0]], [m.ptr for m in keep[1]])
+        src, table = Memory(kv, L * 2 * T * R, 0, 1), Memory(kv, T // P * 4, 1, 1)
+        src.array[:] = np.random.default_rng(R).integers(0, 256, len(src.array), dtype=np.uint8)
+        pages = np.random.default_rng(R).permutation(T // P).astype(np.int32)
+        table.array[:] = pages.view(np.uint8)
+        kv.kvio_load(h, [(src.ptr, T, T, table.ptr)], 0, L)
+        img = np.zeros((2, L, T, R), np.uint8)
+        oracle.load(img[0], img[1], P, [(src.array, T, T, pages)])
+        assert np.array_equal(np.stack([np.stack([m.array.reshape(T, R) for m in row]) for row in keep]), img)
+        assert waves - 4 <= kv._lib.emu_last_waves() <= waves, (R, kv._lib.emu_last_waves())
+        kv.kvio_pool_destroy(h)
+        for m in keep[0] + keep[1] + [src, table]:
+            m.free()
+
+
 @pytest.fixture(scope="module")
 def emulated(tmp_path_factory):
     out = {}
@@ -313,7 +343,8 @@ def test_noalloc_table_in_the_arguments(emulated, name):
     assert r.returncode == 0, r.stdout[-200:] + r.stderr[-3000:]
 
 
-@pytest.mark.parametrize("name,run", [("planes", "run_staged_layers"), ("whole", "run_full_steps")])
+@pytest.mark.parametrize("name,run", [("planes", "run_staged_layers"), ("whole", "run_full_steps"),
+                                      ("whole", "run_default_loads")])
 def test_launch_limits_and_steps(emulated, name, run):
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
             f"import test_emulated_kernels as t\nt.{run}({emulated[name]!r})")
