@@ -422,9 +422,9 @@ void cut_tiles(CopyArgs *a, const Shape &shape, Direction dir) {
     a->transpose = transposes(a->host_layout, shape.lds, a->num_heads, a->row_bytes, shape.tile_kib);
     a->whole_rows = dir == kOffload && !shape.device_scope && !shape.local && a->host_layout != KVIO_HOST_HEAD_MAJOR;
     if (a->whole_rows || a->transpose) {
-        a->tile_vecs = static_cast<int32_t>(most);
-        a->tile_rows = static_cast<int32_t>(
-            std::min<int64_t>(std::max<int64_t>(a->transpose ? most * 16 / a->pitch : most / V, 1), 64));
+        const int64_t row = a->transpose ? a->pitch / 16 : V;
+        a->tile_rows = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(most / row, 1), 64));
+        a->tile_vecs = static_cast<int32_t>(std::min(most, (a->tile_rows * row + 63) / 64 * 64));
         return;
     }
     int64_t unit = 1;                        // cuts lie at multiples of this many vectors
@@ -475,7 +475,7 @@ hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream
         int64_t vecs = 0;                    // of the tile_vecs * plane_tiles a plane's tiles could hold
         for (int32_t i = 0; i < a.n_spans; ++i) vecs += int64_t(a.spans[i].num_tokens) * a.vec_per_row * (a.transpose ? a.num_heads : 1);
         const int64_t room = int64_t(a.plane_tiles) * a.tile_vecs / vecs;
-        const int64_t step = dir == kLoad ? std::max<int64_t>(int64_t(s.tile_kib) * 64, a.tile_vecs) : a.tile_vecs;
+        const int64_t step = dir == kLoad || a.whole_rows || a.transpose ? std::max<int64_t>(int64_t(s.tile_kib) * 64, a.tile_vecs) : a.tile_vecs;
         s.workgroups = static_cast<int>(std::min(s.workgroups * std::max<int64_t>(room, 1) * step / a.tile_vecs, s.workgroups * kMostGrowth));
     }
     // No more waves than tiles, and than the kernels count (far more than the chip holds).

@@ -86,6 +86,7 @@ struct CopyArgs {
     int32_t step_vecs;
     int32_t step_rows;
     int32_t step_cols;
+    int32_t pause;                 // paced offloads: sleep behind a step, in 64 cycles / 2^16 for each vector it moved
     int32_t tile_prefix[KVIO_MAX_SPANS_PER_LAUNCH + 1];
     SpanArg spans[KVIO_MAX_SPANS_PER_LAUNCH];
 };

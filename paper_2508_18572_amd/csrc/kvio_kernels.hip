@@ -35,6 +35,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "kvio_internal.h"
 
 namespace kvio {
@@ -468,6 +470,11 @@ __device__ __forceinline__ void fetch_args(Args &a) {
                  "s"(a.spans[0].page_idx), "s"(a.spans[0].host_tokens), "s"(a.spans[0].num_tokens), "s"(a.spans[0].token0));
 }
 
+// What a wave of a paced offload sleeps behind a step that moved `vecs` vectors.
+__device__ __forceinline__ void rest(Args &a, int vecs) {
+    for (int i = static_cast<int>(static_cast<uint32_t>(a.pause) * static_cast<uint32_t>(vecs) >> 16); i > 0; --i) __builtin_amdgcn_s_sleep(1);
+}
+
 // The copy of one launch.  DIR: kLoad (host chunk -> pool) or kOffload (pool
 // -> host chunk).  U: 16-byte vectors per lane per tile (one tile = up to U
 // KiB per wave).  NT: non-temporal accesses.  SC1: offload host stores with
@@ -529,7 +536,11 @@ __device__ __forceinline__ void copy_tiles(Args &a) {
             const int slot = lane_slot(a, t, lane, lane_page(a, t, lane));
             read_pool<U, NT, WIDE>(a, t, slot, lane, buf);
             write_tile<DIR, U, NT, SC1, WIDE, HL>(a, t, slot, lane, buf);
+            const int moved = t.end;
             t = following(t, more);
+            if constexpr (!SC1) {
+                if (more) rest(a, moved);
+            }
         } while (more);
         return;
     }
@@ -610,17 +621,12 @@ __global__ void __launch_bounds__(kNarrowBound) kvio_head_major_kernel(const Cop
 // nothing tells a wave that the link is full, and what it sends too soon queues
 // ahead of a co-running load's read requests (which PCIe lets pass no posted
 // write).  These waves work in whole-row tiles, one step behind the other: slots,
-// pool reads, host writes as the reads arrive.  Measured at 16 workgroups of one
-// wave with 4 KiB steps, 336 MiB each way, beside a 48-wave load: 92.5 GB/s both
-// ways (46.1 alone); through copy_tiles' offload, plain or overlapped, 74-84
-// (40-51 alone); with device-scope stores and overlap the load takes the whole
-// link and the offload a third (67 until both are done, 55.9 alone).
+// pool reads, host writes as the reads arrive, and a pause (pause_of).  At 16
+// workgroups of one wave with 4 KiB steps, 336 MiB each way, beside a load, they
+// led copy_tiles' offload, plain or overlapped, by 10 to 20 GB/s; with device-scope
+// stores and overlap the load takes the whole link and the offload a third.
+// Head-major offloads on such quotas run in copy_tiles, with the same pause.
 // ----------------------------------------------------------------------------
-// What a paced wave sleeps behind each step, in 64 cycles.  16 waves of 4 KiB
-// steps, alone and beside the load (ms for 336 MiB each way until both are done):
-// 0 6.87 / 8.99, 2 7.08 / 8.52, 4 7.38 / 7.96, 6 7.65 / 7.69, 8 7.95 / 7.96.
-constexpr int kPace = 6;
-
 // To the wave's next tile, if there is one.
 __device__ __forceinline__ bool cursor_next(Args &a, TileCursor &cur) {
     int32_t from = cur.span;
@@ -686,6 +692,7 @@ __global__ void __launch_bounds__((HL != KVIO_HOST_TOKEN_MAJOR ? 256 : 1024)) kv
                       static_cast<int32_t>(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
     if (g >= a.total_tiles) return;
     TileCursor cur = cursor_at(a, g);
+    int moved = 0;                           // vectors of the step before
 #pragma unroll 1
     for (;;) {
         const RowTile t = row_tile(a, cur);
@@ -706,6 +713,8 @@ __global__ void __launch_bounds__((HL != KVIO_HOST_TOKEN_MAJOR ? 256 : 1024)) kv
         const int nvec = t.nrows * a.vec_per_row;
 #pragma unroll 1
         for (int base = 0; base < nvec; base += 64 * U) {
+            rest(a, moved);
+            moved = nvec - base < 64 * U ? nvec - base : 64 * U;
             // Vector k: chunk base + k * 64 (WIDE, all lanes in one row) or this
             // lane's vector of it.
             const int j = base + (WIDE ? 0 : lane);
@@ -742,7 +751,6 @@ __global__ void __launch_bounds__((HL != KVIO_HOST_TOKEN_MAJOR ? 256 : 1024)) kv
                 }
             }
         }
-        __builtin_amdgcn_s_sleep(kPace);
         if (!cursor_next(a, cur)) return;
     }
 }
@@ -883,6 +891,38 @@ static void launch_layout(const CopyArgs &a, dim3 grid, dim3 block, hipStream_t 
     }
 }
 
+// Offloads on a small quota move kPacedMBps and no more: a wave sleeps behind each
+// step for what the step's share of that rate leaves (above some 48 GB/s the
+// link's write side fills, a load's read requests stand behind it, and both ways
+// together fall to 60-75 GB/s).  `takes` is a step's time where few waves run, in ns,
+// taken from steps of 4 to 16 KiB over row sizes: the table's read once a tile, and
+// the rows' way through the wave, longer where rows fill no step or lie apart
+// (head-major).  No sleep where the quota does not reach the rate, and none above
+// 128 KiB in flight, with more than four waves in a workgroup (2 x 1024 threads are
+// bound by their compute units: 53.7 GB/s alone, 33 if they slept too) or more than 24
+// workgroups (some share a load's compute units: 32 x 1 wave moves 60-77 GB/s beside
+// a load with or without).
+// 192 MiB each way, GB/s until both are done | offload alone, with a constant 0.16 us
+// behind each tile and as now:
+//   16 waves x 4 KiB, rows of 1 KiB 91|46.9, 93|47.4; 2 KiB 84|48.9, 89|49.1; 512 bytes
+//     84|51.1, 93|49.2; 8 KiB 72|45.4, 92|47.1; head-major (which had no sleep) 70|52.6, 90|45.6
+//   rows of 1 KiB: 8 waves x 4 KiB 47|23.4, 55|27.4; 12 x 8 KiB 69|55.0, 90|45.6; 16 x 8 77|40.4,
+//     90|45.7; 8 x 16 75|53.0, 92|47.0; 8 workgroups of 4 x 4 KiB 83|45.7, 88|44.5
+constexpr int64_t kPacedInflight = int64_t(128) << 10;
+constexpr int64_t kPacedMBps = 46500;
+constexpr int kPacedWavesPerWg = 4, kPacedWorkgroups = 24;
+
+static int32_t pause_of(const CopyArgs &a, int U) {
+    const int64_t tile = a.whole_rows ? int64_t(a.tile_rows) * a.vec_per_row : a.tile_vecs;
+    const int64_t steps = (tile + 64 * U - 1) / (64 * U), step = std::min<int64_t>(tile, 64 * U);
+    const int64_t inflight = a.waves * step * 16;
+    if (inflight > kPacedInflight || a.waves_per_wg > kPacedWavesPerWg || a.waves > a.waves_per_wg * kPacedWorkgroups) return 0;
+    const int64_t takes = a.host_layout == kHostHeadMajor ? 610 + step * 16 * 153 / 1024
+                                                          : 410 + step * 16 * (step < 64 * U ? 100 : 80) / 1024 + 480 / steps;
+    const int64_t spare = inflight * 1000 / kPacedMBps - takes;
+    return spare <= 0 ? 0 : static_cast<int32_t>((spare << 16) / 26 / step + 1);      // 26 ns: 64 cycles
+}
+
 template <int DIR, int U, bool NT, bool SC1>
 static hipError_t launch_u(CopyArgs &a, const Shape &s, hipStream_t stream) {
     dim3 grid(s.workgroups), block(s.threads);
@@ -900,6 +940,7 @@ static hipError_t launch_u(CopyArgs &a, const Shape &s, hipStream_t stream) {
     a.step_vecs = a.waves * a.tile_vecs;         // used where it stays inside a span
     a.step_rows = a.step_vecs / a.vec_per_row;
     a.step_cols = a.step_vecs % a.vec_per_row;
+    a.pause = DIR == kOffload && !SC1 && !s.local && !a.transpose ? pause_of(a, U) : 0;
     switch (a.host_layout) {
         case kHostPageFirst: launch_layout<DIR, U, NT, SC1, kHostPageFirst>(a, grid, block, stream); break;
         case kHostHeadMajor: launch_layout<DIR, U, NT, SC1, kHostHeadMajor>(a, grid, block, stream); break;

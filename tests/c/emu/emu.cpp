@@ -172,12 +172,13 @@ void *emu_kernarg() { return kernarg; }
 void *emu_lds() { return shared; }
 
 namespace {
-int64_t launches = 0, last_tiles = 0, last_block = 0, last_waves = 0;
+int64_t launches = 0, last_tiles = 0, last_block = 0, last_waves = 0, last_pause = 0;
 }
 extern "C" int64_t emu_launches() { return launches; }
 extern "C" int64_t emu_last_tiles() { return last_tiles; }    // of the last copy kernel
 extern "C" int64_t emu_last_block() { return last_block; }
 extern "C" int64_t emu_last_waves() { return last_waves; }
+extern "C" int64_t emu_last_pause() { return last_pause; }    // behind a step of 256 vectors, in 64 cycles
 // KiB that a default load of `bytes` (rows that fill their steps) keeps in flight.
 extern "C" int64_t emu_default_load_kib(int64_t bytes, int layout) {
     const kvio::Shape s = kvio::default_shape(kvio::kLoad, bytes, layout, true, 8, 256);
@@ -193,6 +194,7 @@ void emu_launch(dim3 grid, dim3 block, size_t lds, const std::function<void()> &
         last_tiles = a.total_tiles;
         last_block = block.x;
         last_waves = a.waves;
+        last_pause = int64_t(a.pause) * 256 >> 16;
         if (a.planes > kvio::kMaxPlanes && a.planes > one_layer) die("more planes than a launch counts", "launch");
     }
     if (w.stacks == nullptr) w.stacks = static_cast<char *>(malloc(kLanes * kStack));

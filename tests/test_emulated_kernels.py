@@ -62,7 +62,7 @@ def load(out):
     kv._lib.emu_alloc.argtypes = [ctypes.c_size_t, ctypes.c_int, ctypes.c_int]
     kv._lib.emu_free.argtypes = [ctypes.c_void_p]
     kv._lib.emu_launches.restype = kv._lib.emu_last_tiles.restype = kv._lib.emu_last_block.restype = ctypes.c_int64
-    kv._lib.emu_last_waves.restype = kv._lib.emu_default_load_kib.restype = ctypes.c_int64
+    kv._lib.emu_last_pause.restype = kv._lib.emu_last_waves.restype = kv._lib.emu_default_load_kib.restype = ctypes.c_int64
     kv._lib.emu_default_load_kib.argtypes = [ctypes.c_int64, ctypes.c_int]
     return kv
 
@@ -314,6 +314,47 @@ def run_default_loads(out):
             m.free()
 
 
+def run_pauses(out):
+    """The pause of offloads on a small quota follows what they keep in flight: none
+    where they do not reach the paced rate, longer the more they exceed it, the same
+    for a byte whatever the row size, in every layout; none for large workgroups,
+    many workgroups, the default grid (also cached) and chunks in device memory."""
+    kv = load(out)
+
+    def pause(layout, De, H, quota, local=0, T=1024):
+        L, P, R = 1, 16, H * De
+        T = max(T, 131072 // R // 16 * 16)
+        keep = [[Memory(kv, T * R, 1, 1) for _ in range(L)] for _ in range(2)]
+        h = kv.kvio_pool_create(L, H, De, 1, P, T, [m.ptr for m in keep[0]], [m.ptr for m in keep[1]], None, kv.launch(*quota), layout)
+        dst, table = Memory(kv, L * 2 * T * R, local, 1), Memory(kv, T // P * 4, 1, 1)
+        for k in range(2):
+            keep[k][0].array[:] = np.random.default_rng(k).integers(0, 256, T * R, dtype=np.uint8)
+        pages = np.random.default_rng(R).permutation(T // P).astype(np.int32)
+        table.array[:] = pages.view(np.uint8)
+        kv.kvio_offload(h, [(dst.ptr, T, T, table.ptr)], 0, L)
+        got, want = kv._lib.emu_last_pause(), np.zeros_like(dst.array)
+        img = np.stack([np.stack([m.array.reshape(T, R) for m in row]) for row in keep])
+        oracle.offload_layout(img[0], img[1], P, [(want, T, T, pages)], LAYOUT[layout], num_heads=H)
+        assert np.array_equal(dst.array, want)
+        kv.kvio_pool_destroy(h)
+        for m in keep[0] + keep[1] + [dst, table]:
+            m.free()
+        return got
+
+    for layout in range(3):
+        at = {q: pause(layout, 256, 2, q) for q in ((8, 64, 4), (12, 64, 4), (16, 64, 4), (24, 64, 4), (8, 256, 4), (32, 64, 4), (0, 0, 0),
+                                                    (0, 0, 0, kv.KVIO_LAUNCH_CACHED), (16, 64, 4, kv.KVIO_LAUNCH_CACHED))}
+        assert at[8, 64, 4] == at[12, 64, 4] == at[32, 64, 4] == at[0, 0, 0] == at[0, 0, 0, 1] == 0, at
+        assert 5 <= at[16, 64, 4] <= 9 and at[16, 64, 4, 1] == at[16, 64, 4], at
+        assert at[24, 64, 4] > 3 * at[16, 64, 4] and at[8, 256, 4] > at[24, 64, 4], at
+        assert pause(layout, 256, 2, (16, 64, 4), local=1) == 0
+    assert pause(0, 512, 1, (2, 1024, 4)) == 0
+    for R in (128, 256, 512, 1024, 4096):
+        assert 5 <= pause(0, R, 1, (16, 64, 4)) <= 9, R
+    assert pause(0, 8192, 1, (16, 64, 4)) > 9                   # one table read for two steps
+    assert pause(0, 16, 1, (8, 256, 4)) == pause(0, 2064, 1, (16, 64, 4)) == 0
+
+
 @pytest.fixture(scope="module")
 def emulated(tmp_path_factory):
     out = {}
@@ -344,7 +385,7 @@ def test_noalloc_table_in_the_arguments(emulated, name):
 
 
 @pytest.mark.parametrize("name,run", [("planes", "run_staged_layers"), ("whole", "run_full_steps"),
-                                      ("whole", "run_default_loads")])
+                                      ("whole", "run_default_loads"), ("whole", "run_pauses")])
 def test_launch_limits_and_steps(emulated, name, run):
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
             f"import test_emulated_kernels as t\nt.{run}({emulated[name]!r})")
