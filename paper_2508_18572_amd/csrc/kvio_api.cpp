@@ -73,13 +73,13 @@ Shape resolve(const kvio_launch &l, const Shape &def) {
     s.nontemporal = (l.flags & KVIO_LAUNCH_CACHED) == 0;
     s.grows = l.workgroups == 0;
     s.local = def.local;
-    s.lds = (l.flags & KVIO_LAUNCH_NO_LDS) == 0;
+    s.lds_below = l.flags & KVIO_LAUNCH_NO_LDS ? 0 : kTransposeBelow;
     s.device_scope = s.nontemporal && !s.local && int64_t(s.workgroups) * (s.threads / 64) * s.tile_kib * 1024 >= kSc1MinInflight;
     return s;
 }
 
 Shape default_shape(const PoolGeom &g, const kvio_launch &l, Direction dir, int64_t bytes) {
-    return default_shape(dir, bytes, g.host_layout, (l.flags & KVIO_LAUNCH_NO_LDS) == 0, g.num_heads, g.seg_bytes);
+    return default_shape(dir, bytes, g.host_layout, l.flags & KVIO_LAUNCH_NO_LDS ? 0 : kTransposeBelow, g.num_heads, g.seg_bytes);
 }
 
 kvio_status check_launch(const kvio_launch &l, const char *which) {
@@ -409,7 +409,8 @@ void common_args(const PoolGeom &g, uint8_t *const *layers, unsigned long long *
     a->host_layout = g.host_layout;
     a->num_heads = g.num_heads;
     cut_tiles(a, shape, dir);
-    a->head_div = divider(a->transpose ? g.row_bytes / 16 : g.num_heads);
+    a->head_div = divider(a->head_groups);
+    a->part_div = divider(int64_t(a->heads_per_tile) * a->vec_per_row);
 }
 
 // Fill in the cut of the vectors of a plane into tiles.
@@ -419,10 +420,19 @@ void cut_tiles(CopyArgs *a, const Shape &shape, Direction dir) {
     a->row_div = divider(V);
     a->vec_step_rows = static_cast<int32_t>(64 / V);
     a->vec_step_cols = static_cast<int32_t>(64 % V);
-    a->transpose = transposes(a->host_layout, shape.lds, a->num_heads, a->row_bytes, shape.tile_kib);
-    a->whole_rows = dir == kOffload && !shape.device_scope && !shape.local && a->host_layout != KVIO_HOST_HEAD_MAJOR;
+    a->transpose = transposes(a->host_layout, shape.lds_below, a->num_heads, a->row_bytes, shape.tile_kib);
+    const bool head_major = a->host_layout == KVIO_HOST_HEAD_MAJOR;
+    a->heads_per_tile = 1;
+    a->head_groups = head_major ? a->num_heads : 1;
+    if (a->transpose) {
+        a->head_groups = static_cast<int32_t>((a->pitch / 16 + most - 1) / most);
+        a->heads_per_tile = (a->num_heads + a->head_groups - 1) / a->head_groups;
+        while (a->heads_per_tile > 1 && a->heads_per_tile * V > most) --a->heads_per_tile;     // segments that do not divide a step
+        a->head_groups = (a->num_heads + a->heads_per_tile - 1) / a->heads_per_tile;
+    }
+    a->whole_rows = dir == kOffload && !shape.device_scope && !shape.local && !head_major;
     if (a->whole_rows || a->transpose) {
-        const int64_t row = a->transpose ? a->pitch / 16 : V;
+        const int64_t row = a->heads_per_tile * V;
         a->tile_rows = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(most / row, 1), 64));
         a->tile_vecs = static_cast<int32_t>(std::min(most, (a->tile_rows * row + 63) / 64 * 64));
         return;
@@ -444,7 +454,7 @@ void cut_tiles(CopyArgs *a, const Shape &shape, Direction dir) {
     // Wide rows begin where their chunk does, page-first rows where their page
     // does: their tiles start at the plane's first vector.
     const bool run = a->host_layout != KVIO_HOST_PAGE_FIRST &&
-                     (a->host_layout == KVIO_HOST_HEAD_MAJOR || V % 64 != 0);
+                     (head_major || V % 64 != 0);
     a->cut_mask = run ? static_cast<int32_t>(15 & ~(unit - 1)) : 0;
     a->cut_bias = static_cast<int32_t>((a->cut_mask + V - 1) / V);
 }
@@ -473,7 +483,7 @@ hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream
     const int64_t waves_per_wg = s.threads / 64;
     if (s.grows) {
         int64_t vecs = 0;                    // of the tile_vecs * plane_tiles a plane's tiles could hold
-        for (int32_t i = 0; i < a.n_spans; ++i) vecs += int64_t(a.spans[i].num_tokens) * a.vec_per_row * (a.transpose ? a.num_heads : 1);
+        for (int32_t i = 0; i < a.n_spans; ++i) vecs += int64_t(a.spans[i].num_tokens) * a.vec_per_row * a.heads_per_tile;
         const int64_t room = int64_t(a.plane_tiles) * a.tile_vecs / vecs;
         const int64_t step = dir == kLoad || a.whole_rows || a.transpose ? std::max<int64_t>(int64_t(s.tile_kib) * 64, a.tile_vecs) : a.tile_vecs;
         s.workgroups = static_cast<int>(std::min(s.workgroups * std::max<int64_t>(room, 1) * step / a.tile_vecs, s.workgroups * kMostGrowth));
@@ -485,8 +495,19 @@ hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream
 }
 
 kvio_status launch_spans(const PoolGeom &g, uint8_t *const *layers, unsigned long long *err, const Resolved *rs,
-                         int32_t n, int32_t l0, int32_t l1, Direction dir, const Shape &shape, hipStream_t stream,
+                         int32_t n, int32_t l0, int32_t l1, Direction dir, Shape shape, hipStream_t stream,
                          const char *fn, uint8_t *const *own_table) {
+    // Short head-major contexts on a fixed grid: a head's run fills half a step or
+    // less, rows of all heads fill it better, through LDS.  32 contexts of 8 heads of
+    // 256 bytes on 16 waves x 4 KiB, by address and through LDS: one token 1635 and
+    // 255 us (offload 1222 and 229), 3 tokens 1650 and 541, 8 tokens 1684 and 1129; 64 heads of
+    // 128 bytes, one token 3305 and 176.  A default grid grows instead, and is ahead
+    // by address (one of 4 tokens: 13.0 against 13.8 us).
+    if (shape.lds_below != 0 && !shape.grows) {
+        int64_t rows = 0, some = 0;
+        for (int32_t i = 0; i < n; ++i) rows += rs[i].num_tokens, some += rs[i].num_tokens != 0;
+        if (some > 0 && rows * g.seg_bytes * 2 <= some * shape.tile_kib * 1024) shape.lds_below = INT32_MAX;
+    }
     CopyArgs a;
     common_args(g, layers, err, shape, dir, l0, &a);
     const int32_t most_spans = own_table != nullptr ? spans_beside_table(g.num_layers) : KVIO_MAX_SPANS_PER_LAUNCH;

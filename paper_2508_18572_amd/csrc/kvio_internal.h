@@ -39,8 +39,8 @@ inline Divider divider(int64_t d) {
 // between calls on different streams.
 //
 // Work decomposition: a "plane" is one run of host rows of the launch's layer
-// range -- a (layer, K|V), or for head-major chunks a (layer, K|V, head) unless
-// the launch transposes --
+// range -- a (layer, K|V), or for head-major chunks a (layer, K|V, head), where the
+// launch transposes a (layer, K|V) and all its heads or a group of them --
 // planes ordered layer-major; a "tile" is tile_vecs consecutive 16-byte vectors
 // of one span in one plane.  tile_prefix[s] is the first tile of span s inside
 // a plane, so a plane holds plane_tiles = tile_prefix[n_spans] tiles and the
@@ -66,7 +66,8 @@ struct CopyArgs {
     int32_t vec_per_row;           // V = row_bytes / 16
     Divider page_div;              // by P
     Divider row_div;               // by V
-    Divider head_div;              // by num_heads; where a launch transposes, by num_heads * V
+    Divider head_div;              // by head_groups
+    Divider part_div;              // by heads_per_tile * V
     Divider plane_div;             // by plane_tiles
     int32_t vec_step_rows;         // 64 / V: rows a lane's vector index advances per 64 vectors
     int32_t vec_step_cols;         // 64 % V: and columns (carried into the row at V)
@@ -78,7 +79,9 @@ struct CopyArgs {
     int32_t n_spans;               // spans in this launch, 1 .. KVIO_MAX_SPANS_PER_LAUNCH
     int32_t host_layout;           // KVIO_HOST_*
     int32_t num_heads;             // H (head-major chunks)
-    int32_t transpose;             // head-major: tiles are tile_rows whole rows of all heads
+    int32_t transpose;             // head-major: tiles are tile_rows rows of heads_per_tile heads
+    int32_t heads_per_tile;        // 1, or where the launch transposes: all heads, or of a row wider than a step, as many as fit
+    int32_t head_groups;           // planes of a (layer, K|V): ceil(H / heads_per_tile) for head-major chunks, else 1
     // Set by launch_copy: waves of a workgroup and of the launch, and the vectors,
     // rows and columns from a wave's tile to its next one.
     int32_t waves_per_wg;
@@ -121,7 +124,7 @@ struct Shape {
     bool device_scope;  // offload host stores with the device-scope (SC1) policy
     bool grows;         // the grid is the library's: it may grow for short spans
     bool local;         // the chunks lie in the memory of the pool's own GPU
-    bool lds;           // head-major chunks: may transpose through LDS
+    int lds_below;      // head-major chunks: segments of fewer 16-byte vectors go through LDS
 };
 
 // Library defaults for the launch shape, chosen by measurement on MI355X
@@ -147,14 +150,14 @@ struct Shape {
 // effect on a background offload beside: 91.4 against 91.3 GB/s both ways), and for
 // loads where rows are too narrow to fill a step (a tile's 64 rows of 16 bytes are 1 KiB).
 constexpr int kDefaultThreads = 256;
-constexpr Shape kDefaultLoad = {13, 192, 4, true, false, false, false, true};
-constexpr Shape kDefaultLoadMiddle = {32, 128, 4, true, false, false, false, true};
-constexpr Shape kDefaultLoadSmall = {16, kDefaultThreads, 4, true, false, false, false, true};
+constexpr Shape kDefaultLoad = {13, 192, 4, true, false, false, false, 0};
+constexpr Shape kDefaultLoadMiddle = {32, 128, 4, true, false, false, false, 0};
+constexpr Shape kDefaultLoadSmall = {16, kDefaultThreads, 4, true, false, false, false, 0};
 constexpr int64_t kMiddleLoadBytes = int64_t(32) << 20;
 constexpr int64_t kSmallLoadBytes = int64_t(4) << 20;
 constexpr int64_t kSmallLoadBytesPageFirst = int64_t(512) << 10;
-constexpr Shape kDefaultOffload = {32, kDefaultThreads, 16, true, false, false, false, true};
-constexpr Shape kDefaultOffloadPageFirst = {64, kDefaultThreads, 8, true, false, false, false, true};
+constexpr Shape kDefaultOffload = {32, kDefaultThreads, 16, true, false, false, false, 0};
+constexpr Shape kDefaultOffloadPageFirst = {64, kDefaultThreads, 8, true, false, false, false, 0};
 constexpr int64_t kMostGrowth = 8;
 // Head-major chunks whose segments are narrower than this many 16-byte vectors go
 // through LDS.  By address (a tile is one head's run of up to 64 rows) a step of
@@ -170,24 +173,24 @@ constexpr int64_t kMostGrowth = 8;
 // of 8 KiB steps at every size: 48 are 5% slower, 4 KiB steps 45% (the host runs of
 // a tile are its step divided by the heads).
 constexpr int kTransposeBelow = 4;
-constexpr Shape kDefaultLoadTranspose = {16, 128, 8, true, false, false, false, true};
-inline bool transposes(int host_layout, bool lds, int num_heads, int64_t seg_bytes, int tile_kib) {
-    return host_layout == KVIO_HOST_HEAD_MAJOR && lds && seg_bytes < kTransposeBelow * 16 && num_heads > 1 &&
-           num_heads * seg_bytes <= int64_t(tile_kib) * 1024;
+constexpr Shape kDefaultLoadTranspose = {16, 128, 8, true, false, false, false, 0};
+inline bool transposes(int host_layout, int lds_below, int num_heads, int64_t seg_bytes, int tile_kib) {
+    return host_layout == KVIO_HOST_HEAD_MAJOR && num_heads > 1 && seg_bytes < int64_t(lds_below) * 16 &&
+           (lds_below > kTransposeBelow || num_heads * seg_bytes <= int64_t(tile_kib) * 1024);
 }
 // Chunks in the memory of the pool's own GPU (a copy between two caches, a gather
 // for a consumer there): nothing crosses the host link, so the whole chip copies,
 // with the compiler's stores.  256 MiB of 2 KiB rows in 90-93 us each way (5.9 TB/s
 // read and written) where the shapes and stores for host memory took 2039 and 587;
 // 256 to 2048 workgroups and steps of 4 to 16 KiB differ by 5%.
-constexpr Shape kDefaultLocal = {1024, kDefaultThreads, 4, true, false, false, true, true};
+constexpr Shape kDefaultLocal = {1024, kDefaultThreads, 4, true, false, false, true, 0};
 
 // The default shape of a call that moves `bytes` in direction `dir` between
 // the pool and host chunks of layout `host_layout` (KVIO_HOST_*), head-major ones
 // with `num_heads` segments of `seg_bytes`.
-inline Shape default_shape(int dir, int64_t bytes, int host_layout, bool lds, int num_heads, int64_t seg_bytes) {
+inline Shape default_shape(int dir, int64_t bytes, int host_layout, int lds_below, int num_heads, int64_t seg_bytes) {
     if (dir != 0) return host_layout == KVIO_HOST_PAGE_FIRST ? kDefaultOffloadPageFirst : kDefaultOffload;
-    if (transposes(host_layout, lds, num_heads, seg_bytes, kDefaultLoadTranspose.tile_kib)) return kDefaultLoadTranspose;
+    if (transposes(host_layout, lds_below, num_heads, seg_bytes, kDefaultLoadTranspose.tile_kib)) return kDefaultLoadTranspose;
     const int64_t small = host_layout == KVIO_HOST_PAGE_FIRST ? kSmallLoadBytesPageFirst : kSmallLoadBytes;
     return bytes < small ? kDefaultLoadSmall : bytes < kMiddleLoadBytes ? kDefaultLoadMiddle : kDefaultLoad;
 }
@@ -206,7 +209,7 @@ constexpr int64_t kSc1MinInflight = KVIO_SC1_MIN_INFLIGHT;
 // Staged transfers: the scatter / gather between the HBM staging buffer and
 // the pool is HBM-bound, so it takes the whole chip (4 GiB of 2 KiB rows at
 // page size 1 in 1.75 ms, 2.4 TB/s of payload).
-constexpr Shape kDefaultStaged = {1024, kDefaultThreads, 16, true, false, false, true, true};
+constexpr Shape kDefaultStaged = {1024, kDefaultThreads, 16, true, false, false, true, 0};
 
 // Fill in how the vectors of a plane are cut into tiles, from row_bytes and
 // host_layout: tiles of up to tile_kib KiB that touch at most 64 rows (a lane

@@ -216,7 +216,7 @@ __device__ __forceinline__ Tile locate(Args &a, const TileCursor &c) {
     int32_t lkv = c.plane, head = 0;
     if constexpr (HL == kHostHeadMajor) {
         lkv = static_cast<int32_t>(div_small(static_cast<uint32_t>(c.plane), a.head_div));
-        head = c.plane - lkv * a.num_heads;
+        head = c.plane - lkv * a.head_groups;
     }
     lkv += a.layer_begin * 2;
     t.span = c.span;
@@ -643,15 +643,17 @@ __device__ __forceinline__ bool cursor_next(Args &a, TileCursor &cur) {
 }
 
 struct RowTile {
-    int span, layer, kv;
+    int span, layer, kv, group;              // group: of heads, where the launch transposes
     int t0, nrows;                           // first row in the span, and rows
 };
 
 __device__ __forceinline__ RowTile row_tile(Args &a, const TileCursor &c) {
     RowTile t;
     t.span = c.span;
-    t.layer = a.layer_begin + (c.plane >> 1);
-    t.kv = c.plane & 1;
+    const int lkv = static_cast<int>(div_small(static_cast<uint32_t>(c.plane), a.head_div));
+    t.group = c.plane - lkv * a.head_groups;
+    t.layer = a.layer_begin + (lkv >> 1);
+    t.kv = lkv & 1;
     t.t0 = (c.w - a.tile_prefix[c.span]) * a.tile_rows;
     const int left = a.spans[c.span].num_tokens - t.t0;
     t.nrows = left < a.tile_rows ? left : a.tile_rows;
@@ -756,13 +758,15 @@ __global__ void __launch_bounds__((HL != KVIO_HOST_TOKEN_MAJOR ? 256 : 1024)) kv
 }
 
 // ----------------------------------------------------------------------------
-// Head-major chunks of narrow segments (kTransposeBelow), through LDS.  A wave
-// owns a tile of n whole rows that fits its U KiB of LDS.  It reads the tile in
+// Head-major chunks of narrow segments or few tokens, through LDS.  A wave owns a
+// tile of n whole rows (of a row wider than a step, n is 1 and the tile a part of its
+// heads) that fits its U KiB of LDS.  It reads the tile in
 // host order (per head, n * De contiguous bytes), writes each vector to its
 // place in pool order in its slice, and reads the slice back in pool order, so
 // both sides are runs: host reads of n * De bytes, pool writes of whole rows.
-// Offloads run the same two phases the other way round.  With Vd = De / 16:
-//   pool order  p = (r * H + h) * Vd + c     (row r, head h, vector c)
+// Offloads run the same two phases the other way round.  With Vd = De / 16 and V
+// the vectors of a row of the tile:
+//   pool order  p = r * V + h * Vd + c       (row r, head h, vector c)
 //   host order  q = (h * n + r) * Vd + c
 // A tile's page-table entries are read a tile ahead, as in copy_tiles.
 // ----------------------------------------------------------------------------
@@ -775,7 +779,7 @@ __global__ void __launch_bounds__(kNarrowBound) kvio_head_transpose_kernel(const
     const int32_t g = static_cast<int32_t>(blockIdx.x) * a.waves_per_wg + wave_in_wg;
     if (g >= a.total_tiles) return;
     u32x4 *slice = lds + wave_in_wg * (U * 64);
-    const int Vd = a.vec_per_row, V = a.num_heads * Vd;
+    const int Vd = a.vec_per_row;
     // The wave's lanes exchange data through its slice: what was written is there.
     auto exchange = [] {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -798,11 +802,13 @@ __global__ void __launch_bounds__(kNarrowBound) kvio_head_transpose_kernel(const
     for (;; t = next) {
         Span &sp = a.spans[t.span];
         const int32_t lkv = t.layer * 2 + t.kv;
-        uint8_t *pool = pool_layer(a, lkv);
-        const int n = t.nrows, nvec = n * V;
+        const int head0 = t.group * a.heads_per_tile;
+        const int heads = a.num_heads - head0 < a.heads_per_tile ? a.num_heads - head0 : a.heads_per_tile;
+        uint8_t *pool = pool_layer(a, lkv) + head0 * a.row_bytes;
+        const int n = t.nrows, V = heads * Vd, nvec = n * V;      // the last group may be smaller; n is 1 where there are several
         const int64_t head_stride = sp.host_tokens * a.row_bytes;
-        // Head 0's run at the tile's first row.
-        uint8_t *host = const_cast<uint8_t *>(sp.host) + static_cast<int64_t>(lkv) * a.num_heads * head_stride + t.t0 * a.row_bytes;
+        // The first head's run at the tile's first row.
+        uint8_t *host = const_cast<uint8_t *>(sp.host) + (static_cast<int64_t>(lkv) * a.num_heads + head0) * head_stride + t.t0 * a.row_bytes;
         // Vector q of the tile in host order: its place in pool order, its row and
         // its byte offset from `host`.
         struct Host { int pool, r; int64_t off; };
@@ -832,7 +838,7 @@ __global__ void __launch_bounds__(kNarrowBound) kvio_head_transpose_kernel(const
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 const int p = k * 64 + lane;
-                const int r = static_cast<int>(div_small(static_cast<uint32_t>(p), a.head_div));
+                const int r = static_cast<int>(div_small(static_cast<uint32_t>(p), a.part_div));
                 const int s = __shfl(slot, r & 63);
                 if (p < nvec && s >= 0) store16<NT>(pool + s * a.pitch + (p - r * V) * 16, slice[p]);
             }
@@ -841,7 +847,7 @@ __global__ void __launch_bounds__(kNarrowBound) kvio_head_transpose_kernel(const
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 const int p = k * 64 + lane;
-                const int r = static_cast<int>(div_small(static_cast<uint32_t>(p), a.head_div));
+                const int r = static_cast<int>(div_small(static_cast<uint32_t>(p), a.part_div));
                 const int s = __shfl(slot, r & 63);
                 buf[k] = load16<NT>(pool + (p < nvec && s >= 0 ? s * a.pitch + (p - r * V) * 16 : 0));
             }
@@ -897,30 +903,29 @@ static void launch_layout(const CopyArgs &a, dim3 grid, dim3 block, hipStream_t 
 // together fall to 60-75 GB/s).  `takes` is a step's time where few waves run, in ns,
 // taken from steps of 4 to 16 KiB over row sizes: the table's read once a tile, and
 // the rows' way through the wave, longer where rows fill no step or lie apart
-// (head-major).  No sleep where the quota does not reach the rate, and none above
-// 128 KiB in flight, with more than four waves in a workgroup (2 x 1024 threads are
-// bound by their compute units: 53.7 GB/s alone, 33 if they slept too) or more than 24
-// workgroups (some share a load's compute units: 32 x 1 wave moves 60-77 GB/s beside
-// a load with or without).
+// (head-major).  No sleep where the quota does not reach the rate, none of more than
+// kPacedSleep ns (the waves of such quotas wait for one another long before: 8
+// workgroups of 4 waves x 4 KiB moved 2 MiB in 80 us, without 60), and none with more
+// than four waves in a workgroup (2 x 1024 threads are bound by their compute units:
+// 53.7 GB/s alone, 33 if they slept too).
 // 192 MiB each way, GB/s until both are done | offload alone, with a constant 0.16 us
 // behind each tile and as now:
-//   16 waves x 4 KiB, rows of 1 KiB 91|46.9, 93|47.4; 2 KiB 84|48.9, 89|49.1; 512 bytes
-//     84|51.1, 93|49.2; 8 KiB 72|45.4, 92|47.1; head-major (which had no sleep) 70|52.6, 90|45.6
-//   rows of 1 KiB: 8 waves x 4 KiB 47|23.4, 55|27.4; 12 x 8 KiB 69|55.0, 90|45.6; 16 x 8 77|40.4,
-//     90|45.7; 8 x 16 75|53.0, 92|47.0; 8 workgroups of 4 x 4 KiB 83|45.7, 88|44.5
-constexpr int64_t kPacedInflight = int64_t(128) << 10;
+//   16 waves x 4 KiB, rows of 1 KiB 91|46.7, 93|47.2; 2 KiB 83|48.7, 90|48.9; 512 bytes
+//     83|50.8, 94|48.7; 8 KiB 71|45.0, 92|46.9; head-major (which had no sleep) 70|54.8, 90|46.1
+//   rows of 1 KiB: 8 waves x 4 KiB 47|23.4, 55|27.4; 12 x 8 KiB 69|54.6, 90|45.3; 8 x 16 75|52.8,
+//     91|46.4; no sleep: 16 x 8 77|40.2, 79|43.9, 8 workgroups of 4 x 4 KiB 83|45.5, 78|48.8
 constexpr int64_t kPacedMBps = 46500;
-constexpr int kPacedWavesPerWg = 4, kPacedWorkgroups = 24;
+constexpr int64_t kPacedSleep = 700;
+constexpr int kPacedWavesPerWg = 4;
 
 static int32_t pause_of(const CopyArgs &a, int U) {
     const int64_t tile = a.whole_rows ? int64_t(a.tile_rows) * a.vec_per_row : a.tile_vecs;
     const int64_t steps = (tile + 64 * U - 1) / (64 * U), step = std::min<int64_t>(tile, 64 * U);
-    const int64_t inflight = a.waves * step * 16;
-    if (inflight > kPacedInflight || a.waves_per_wg > kPacedWavesPerWg || a.waves > a.waves_per_wg * kPacedWorkgroups) return 0;
+    if (a.waves_per_wg > kPacedWavesPerWg) return 0;
     const int64_t takes = a.host_layout == kHostHeadMajor ? 610 + step * 16 * 153 / 1024
                                                           : 410 + step * 16 * (step < 64 * U ? 100 : 80) / 1024 + 480 / steps;
-    const int64_t spare = inflight * 1000 / kPacedMBps - takes;
-    return spare <= 0 ? 0 : static_cast<int32_t>((spare << 16) / 26 / step + 1);      // 26 ns: 64 cycles
+    const int64_t spare = a.waves * step * 16 * 1000 / kPacedMBps - takes;
+    return spare <= 0 || spare > kPacedSleep ? 0 : static_cast<int32_t>((spare << 16) / 26 / step + 1);      // 26 ns: 64 cycles
 }
 
 template <int DIR, int U, bool NT, bool SC1>

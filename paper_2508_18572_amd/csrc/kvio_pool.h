@@ -61,9 +61,7 @@ kvio_status check_launch(const kvio_launch &l, const char *which);
 Shape resolve(const kvio_launch &l, const Shape &def);
 Shape default_shape(const PoolGeom &g, const kvio_launch &l, Direction dir, int64_t bytes);
 // Planes of `layers` layers in a launch.
-inline int64_t planes(const CopyArgs &a, int64_t layers) {
-    return layers * 2 * (a.host_layout == KVIO_HOST_HEAD_MAJOR && !a.transpose ? a.num_heads : 1);
-}
+inline int64_t planes(const CopyArgs &a, int64_t layers) { return layers * 2 * a.head_groups; }
 // Device-visible address of [p, p + bytes) (see kvio_api.cpp).
 kvio_status device_view(const void *p, uint64_t bytes, bool want_device_memory, const char *what,
                         const uint8_t **out, int *device = nullptr);
@@ -80,7 +78,7 @@ hipError_t launch_capped(CopyArgs &a, Direction dir, Shape s, hipStream_t stream
 // addresses in host memory, `layers` null) each launch carries the table in its
 // arguments and takes spans_beside_table(L) spans, which must be at least one.
 kvio_status launch_spans(const PoolGeom &g, uint8_t *const *layers, unsigned long long *err, const Resolved *rs,
-                         int32_t n, int32_t l0, int32_t l1, Direction dir, const Shape &shape, hipStream_t stream,
+                         int32_t n, int32_t l0, int32_t l1, Direction dir, Shape shape, hipStream_t stream,
                          const char *fn, uint8_t *const *own_table = nullptr);
 // KVIO_LAUNCH_STAGED transfers (kvio_staged.cpp).
 kvio_status run_staged(kvio_pool_t p, const std::vector<Resolved> &rs, const kvio_span *spans, int32_t n,

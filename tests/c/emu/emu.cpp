@@ -181,7 +181,7 @@ extern "C" int64_t emu_last_waves() { return last_waves; }
 extern "C" int64_t emu_last_pause() { return last_pause; }    // behind a step of 256 vectors, in 64 cycles
 // KiB that a default load of `bytes` (rows that fill their steps) keeps in flight.
 extern "C" int64_t emu_default_load_kib(int64_t bytes, int layout) {
-    const kvio::Shape s = kvio::default_shape(kvio::kLoad, bytes, layout, true, 8, 256);
+    const kvio::Shape s = kvio::default_shape(kvio::kLoad, bytes, layout, kvio::kTransposeBelow, 8, 256);
     return int64_t(s.workgroups) * (s.threads / 64) * s.tile_kib;
 }
 
@@ -190,7 +190,7 @@ void emu_launch(dim3 grid, dim3 block, size_t lds, const std::function<void()> &
     ++launches;
     if (bytes == sizeof(kvio::CopyArgs)) {
         const auto &a = *static_cast<const kvio::CopyArgs *>(arg);
-        const int64_t one_layer = a.host_layout == KVIO_HOST_HEAD_MAJOR && !a.transpose ? 2 * a.num_heads : 2;
+        const int64_t one_layer = 2 * a.head_groups;
         last_tiles = a.total_tiles;
         last_block = block.x;
         last_waves = a.waves;

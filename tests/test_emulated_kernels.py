@@ -318,7 +318,7 @@ def run_pauses(out):
     """The pause of offloads on a small quota follows what they keep in flight: none
     where they do not reach the paced rate, longer the more they exceed it, the same
     for a byte whatever the row size, in every layout; none for large workgroups,
-    many workgroups, the default grid (also cached) and chunks in device memory."""
+    quotas far above the rate, the default grid (also cached) and chunks in device memory."""
     kv = load(out)
 
     def pause(layout, De, H, quota, local=0, T=1024):
@@ -342,17 +342,69 @@ def run_pauses(out):
         return got
 
     for layout in range(3):
-        at = {q: pause(layout, 256, 2, q) for q in ((8, 64, 4), (12, 64, 4), (16, 64, 4), (24, 64, 4), (8, 256, 4), (32, 64, 4), (0, 0, 0),
+        at = {q: pause(layout, 256, 2, q) for q in ((8, 64, 4), (12, 64, 4), (16, 64, 4), (20, 64, 4), (4, 256, 4), (8, 256, 4), (32, 64, 4), (0, 0, 0),
                                                     (0, 0, 0, kv.KVIO_LAUNCH_CACHED), (16, 64, 4, kv.KVIO_LAUNCH_CACHED))}
-        assert at[8, 64, 4] == at[12, 64, 4] == at[32, 64, 4] == at[0, 0, 0] == at[0, 0, 0, 1] == 0, at
-        assert 5 <= at[16, 64, 4] <= 9 and at[16, 64, 4, 1] == at[16, 64, 4], at
-        assert at[24, 64, 4] > 3 * at[16, 64, 4] and at[8, 256, 4] > at[24, 64, 4], at
+        assert at[8, 64, 4] == at[12, 64, 4] == at[32, 64, 4] == at[8, 256, 4] == at[0, 0, 0] == at[0, 0, 0, 1] == 0, at
+        assert 5 <= at[16, 64, 4] <= 9 and at[16, 64, 4, 1] == at[16, 64, 4] == at[4, 256, 4], at
+        assert at[20, 64, 4] > 2 * at[16, 64, 4], at
         assert pause(layout, 256, 2, (16, 64, 4), local=1) == 0
     assert pause(0, 512, 1, (2, 1024, 4)) == 0
     for R in (128, 256, 512, 1024, 4096):
         assert 5 <= pause(0, R, 1, (16, 64, 4)) <= 9, R
     assert pause(0, 8192, 1, (16, 64, 4)) > 9                   # one table read for two steps
     assert pause(0, 16, 1, (8, 256, 4)) == pause(0, 2064, 1, (16, 64, 4)) == 0
+
+
+def run_short_contexts(out):
+    """Short head-major contexts on a fixed quota: a wave's step holds the rows of all
+    heads (or of as many as fit), not one head's few vectors; long contexts, the
+    default grid and KVIO_LAUNCH_NO_LDS go by address."""
+    kv = load(out)
+    P = 4
+    for De, H, T, n, kib, most in ((256, 8, 1, 3, 4, 1.0), (256, 8, 3, 2, 4, 2.1), (128, 64, 1, 2, 4, 2.0), (128, 64, 2, 1, 4, 4.0),
+                                   (64, 5, 4, 5, 16, 1.0), (160, 60, 1, 2, 8, 2.0), (16, 300, 7, 1, 4, None), (1040, 7, 1, 2, 4, None)):
+        L, R, rng = 2, H * De, np.random.default_rng(H)
+        S, cap = (n * -(-T // P) + 1) * P, T + 1
+        img = rng.integers(0, 256, size=(2, L, S, R), dtype=np.uint8)
+        perm, keep = rng.permutation(S // P).astype(np.int32), []
+        for quota in ((2, 64, kib), (2, 64, kib, kv.KVIO_LAUNCH_NO_LDS), (0, 0, 0)):
+            pool = [[Memory(kv, S * R, 1, 1) for _ in range(L)] for _ in range(2)]
+            for k in range(2):
+                for l in range(L):
+                    pool[k][l].array[:] = img[k, l].reshape(-1)
+            mode, spans, ora, outs = kv.launch(*quota), [], [], []
+            h = kv.kvio_pool_create(L, H, De, 1, P, S, [m.ptr for m in pool[0]], [m.ptr for m in pool[1]], mode, mode, 2)
+            for i in range(n):
+                src, dst, table = Memory(kv, L * 2 * cap * R, 0, 1), Memory(kv, L * 2 * cap * R, 0, 0), Memory(kv, 16, 1, 1)
+                src.array[:], dst.array[:] = rng.integers(0, 256, len(src.array), dtype=np.uint8), 0x55
+                pages = perm[i * -(-T // P):(i + 1) * -(-T // P)].copy()
+                table.array[:4 * len(pages)] = pages.view(np.uint8)
+                spans.append((src.ptr, cap, T, table.ptr)), ora.append((src.array, cap, T, pages)), outs.append((dst, table))
+                keep += [src, dst, table]
+            kv.kvio_load(h, spans, 0, L)
+            tiles, exp = kv._lib.emu_last_tiles(), img.copy()
+            oracle.load_layout(exp[0], exp[1], P, ora, LAYOUT[2], num_heads=H)
+            assert np.array_equal(np.stack([np.stack([m.array.reshape(S, R) for m in row]) for row in pool]), exp), (De, H, T, quota)
+            kv.kvio_offload(h, [(o[0].ptr, cap, T, o[1].ptr) for o in outs], 0, L)
+            for (dst, _), (_, _, _, pages) in zip(outs, ora):
+                want = np.full(len(dst.array), 0x55, np.uint8)
+                oracle.offload_layout(exp[0], exp[1], P, [(want, cap, T, pages)], LAYOUT[2], num_heads=H)
+                assert np.array_equal(dst.array, want), (De, H, T, quota)
+            if quota == (2, 64, kib) and most is not None:
+                assert tiles <= most * L * 2 * n and kv._lib.emu_last_tiles() == tiles, (De, H, T, tiles)
+            elif quota != (2, 64, kib) and De >= 64:
+                assert tiles >= L * 2 * n * H, (De, H, T, quota, tiles)
+            kv.kvio_pool_destroy(h)
+            keep += pool[0] + pool[1]
+        for m in keep:
+            m.free()
+    D = 64                                       # nothing to move: nothing launched
+    pool = [Memory(kv, 4 * 2 * D, 1, 1) for _ in range(2)]
+    h = kv.kvio_pool_create(1, 2, D, 1, 4, 4, [pool[0].ptr], [pool[1].ptr], kv.launch(1, 64, 4), kv.launch(1, 64, 4), 2)
+    before = kv._lib.emu_launches()
+    kv.kvio_load(h, [(0, 0, 0, 0)], 0, 1)
+    assert kv._lib.emu_launches() == before
+    kv.kvio_pool_destroy(h)
 
 
 @pytest.fixture(scope="module")
@@ -385,7 +437,8 @@ def test_noalloc_table_in_the_arguments(emulated, name):
 
 
 @pytest.mark.parametrize("name,run", [("planes", "run_staged_layers"), ("whole", "run_full_steps"),
-                                      ("whole", "run_default_loads"), ("whole", "run_pauses")])
+                                      ("whole", "run_default_loads"), ("whole", "run_pauses"),
+                                      ("whole", "run_short_contexts")])
 def test_launch_limits_and_steps(emulated, name, run):
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
             f"import test_emulated_kernels as t\nt.{run}({emulated[name]!r})")

@@ -111,6 +111,15 @@ def test_head_major_narrow_segments(kv, H, De, tile):
     run_layout_case(kv, 2, 2, H, De // 2, 5, 500, spans, l0=0, l1=2, launch=kv.launch(3 if tile else 0, 0, tile), seed=H + De)
 
 
+@pytest.mark.parametrize("wg,threads,tile", [(16, 64, 4), (3, 256, 8), (2, 1024, 16)])
+@pytest.mark.parametrize("H,De", [(8, 256), (64, 128), (60, 160), (7, 1040)])
+def test_head_major_short_contexts_on_a_quota(kv, H, De, wg, threads, tile):
+    """Contexts of a few tokens on a fixed grid go through LDS in tiles of rows of all
+    heads, of rows wider than a step in tiles of some of them."""
+    spans = [(1, 1), (3, 5), (0, 1), (2, 2), (1, 4)]
+    run_layout_case(kv, 2, 3, H, De // 2, 3, 60, spans, l0=1, l1=3, launch=kv.launch(wg, threads, tile), seed=H + tile)
+
+
 @pytest.mark.parametrize("wg,threads,tile", [(1, 64, 4), (5, 1024, 16), (64, 256, 8)])
 @pytest.mark.parametrize("layout", [1, 2])
 def test_layout_launch_shapes_and_subrange(kv, layout, wg, threads, tile):
