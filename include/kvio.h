@@ -103,7 +103,16 @@ typedef enum kvio_status {
 
 /* Launch shaping (Sec. 4.2: a small number of large workgroups keeps the I/O
  * kernel on few compute units; cache bypass limits pollution).  Zero fields
- * take the library defaults.  Results never depend on these. */
+ * take the library defaults: loads 13 workgroups of three waves, below 32 MiB 16
+ * of four or 32 of two, offloads 32 or 64 of four.  Two defaults take more of the GPU, and
+ * workgroups != 0 turns both off.  Where every chunk of a call lies in the
+ * memory of the pool's own GPU (handles only), nothing crosses the host link and the call takes 1024
+ * workgroups.  Where contexts are so short, or rows so narrow, that a wave's
+ * steps are mostly empty, the grid grows up to 8 times.
+ * An offload whose waves x step come to about 64 to 128 KiB (16 workgroups of one
+ * wave with 4 KiB steps) is a background quota: it moves 46.5 GB/s at most, the
+ * rate that leaves a load beside it most of the link.
+ * Results never depend on these. */
 #define KVIO_LAUNCH_CACHED 0x1     /* plain loads/stores instead of non-temporal ones */
 #define KVIO_LAUNCH_NO_LDS 0x2     /* head-major chunks of segments below 64 bytes: by address, not through LDS
                                       (the others never use LDS) */

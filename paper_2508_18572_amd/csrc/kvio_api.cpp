@@ -499,10 +499,10 @@ kvio_status launch_spans(const PoolGeom &g, uint8_t *const *layers, unsigned lon
                          const char *fn, uint8_t *const *own_table) {
     // Short head-major contexts on a fixed grid: a head's run fills half a step or
     // less, rows of all heads fill it better, through LDS.  32 contexts of 8 heads of
-    // 256 bytes on 16 waves x 4 KiB, by address and through LDS: one token 1635 and
-    // 255 us (offload 1222 and 229), 3 tokens 1650 and 541, 8 tokens 1684 and 1129; 64 heads of
-    // 128 bytes, one token 3305 and 176.  A default grid grows instead, and is ahead
-    // by address (one of 4 tokens: 13.0 against 13.8 us).
+    // 256 bytes on 16 waves x 4 KiB, by address and through LDS: one token 1621 and
+    // 258 us (offload 1216 and 236), 3 tokens 1636 and 548, 8 tokens 1671 and 1098; 64 heads of
+    // 128 bytes, one token 3293 and 138 (offload 2370 and 156).  A default grid grows
+    // instead and stays by address.
     if (shape.lds_below != 0 && !shape.grows) {
         int64_t rows = 0, some = 0;
         for (int32_t i = 0; i < n; ++i) rows += rs[i].num_tokens, some += rs[i].num_tokens != 0;

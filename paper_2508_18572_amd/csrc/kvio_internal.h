@@ -198,7 +198,9 @@ inline Shape default_shape(int dir, int64_t bytes, int host_layout, int lds_belo
 // store into host memory with the SC1 policy: enough to cover the longer
 // acknowledgement of those stores, so the link runs at its full write rate (57.0
 // against 55.7 GB/s at the default 128 waves x 16 KiB).  Smaller quotas (16 waves
-// x 4 KiB: 27 against 44 GB/s) keep the plain policy.  A build may move the
+// x 4 KiB: 27 against 44 GB/s) keep the plain policy.  The quota decides and not what
+// a short call leaves of it: default offloads of 32 to 512 KiB take 4.0-12.5 us with
+// SC1 and 4.6-13.1 with plain stores (page-first of 2 MiB alone 41.3 and 40.2).  A build may move the
 // threshold (-DKVIO_SC1_MIN_INFLIGHT=0 stores every offload with SC1; a huge value
 // never does), which is how both policies were measured over launch shapes.
 #ifndef KVIO_SC1_MIN_INFLIGHT

@@ -905,7 +905,7 @@ static void launch_layout(const CopyArgs &a, dim3 grid, dim3 block, hipStream_t 
 // the rows' way through the wave, longer where rows fill no step or lie apart
 // (head-major).  No sleep where the quota does not reach the rate, none of more than
 // kPacedSleep ns (the waves of such quotas wait for one another long before: 8
-// workgroups of 4 waves x 4 KiB moved 2 MiB in 80 us, without 60), and none with more
+// workgroups of 4 waves x 4 KiB moved 2 MiB in 80 us, without in 56), and none with more
 // than four waves in a workgroup (2 x 1024 threads are bound by their compute units:
 // 53.7 GB/s alone, 33 if they slept too).
 // 192 MiB each way, GB/s until both are done | offload alone, with a constant 0.16 us

@@ -403,8 +403,7 @@ def test_out_of_range_page_is_skipped_and_reported(kv):
 @pytest.mark.parametrize("tile", [4, 8, 16])
 def test_out_of_range_page_every_layout_and_step(kv, layout, tile):
     """The range check on every host layout and step size, both directions
-    (head-major loads with steps of 8 KiB or more check the page after their
-    host reads are issued).  Expected images come from the oracle run on a
+    (loads check a tile's pages after its host reads are issued).  Expected images come from the oracle run on a
     pool one page larger, where the bad index is a valid page: its first S
     slots are the GPU pool after the load, and the offload leaves untouched
     exactly the host bytes that page would supply (found by running the

@@ -140,7 +140,7 @@ def test_workload3_staged_layerwise(kv, io_stream):
 @pytest.mark.parametrize("k,layout,layerwise", [(2, "head", False), (3, "page", True)],
                          ids=["workload2_head_major", "workload3_page_first_layerwise"])
 def test_other_host_layouts_at_full_size(kv, io_stream, k, layout, layerwise):
-    """The head/token transpose (head-major chunks, through LDS) on workload 2
+    """The head/token transpose (head-major chunks, by address) on workload 2
     and the paper's page-first chunks on workload 3 loaded layer by layer, at
     full size in the default launch shapes: the whole pool image against the
     oracle's load of the same chunks, layer by layer, and the offload's round
