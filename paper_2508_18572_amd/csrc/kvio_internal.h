@@ -89,7 +89,7 @@ struct CopyArgs {
     int32_t step_vecs;
     int32_t step_rows;
     int32_t step_cols;
-    int32_t pause;                 // paced offloads: sleep behind a step, in 64 cycles / 2^16 for each vector it moved
+    int32_t pause;                 // sleep behind a step, in 64 cycles / 2^16 for each vector it moved
     int32_t tile_prefix[KVIO_MAX_SPANS_PER_LAUNCH + 1];
     SpanArg spans[KVIO_MAX_SPANS_PER_LAUNCH];
 };
@@ -128,12 +128,10 @@ struct Shape {
 };
 
 // Library defaults for the launch shape, chosen by measurement on MI355X
-// (PCIe Gen5 x16 host link), on 13 of the 256 CUs for large loads.
-//   Load of 32 MiB or more: 13 workgroups x 3 waves, 4 KiB steps (156 KiB in
-//   flight): 57.3 GB/s, where 48 waves reach 57.5.  More reads in flight slow what
-//   runs beside them: a 1M-token load beside a background offload moves 98.4 GB/s
-//   both ways with 39 waves, 96.7 with 42, 95.7 with 45, 95.0 with 48, of which the
-//   load 52.5, 50.7, 49.8, 49.4.
+// (PCIe Gen5 x16 host link), on 16 of the 256 CUs for large loads.
+//   Load of 32 MiB or more: 16 workgroups x 3 waves, 4 KiB steps (192 KiB in
+//   flight), which pause between steps (load_pause): 57.5 GB/s alone, beside a
+//   background offload 102.5 both ways.  39 waves reach 57.2-57.4 and 102.6.
 //   Loads below that: 64 waves, 16 x 4 below 4 MiB and 32 x 2 above.  48 waves take
 //   as long alone (2 MiB of 512-byte rows 40.1 against 40.4 us), but on two streams,
 //   each with contexts of its own, 1.5 to 3% longer at every size (8 MiB: 155 against
@@ -150,10 +148,14 @@ struct Shape {
 // effect on a background offload beside: 91.4 against 91.3 GB/s both ways), and for
 // loads where rows are too narrow to fill a step (a tile's 64 rows of 16 bytes are 1 KiB).
 constexpr int kDefaultThreads = 256;
-constexpr Shape kDefaultLoad = {13, 192, 4, true, false, false, false, 0};
+constexpr Shape kDefaultLoad = {16, 192, 4, true, false, false, false, 0};
 constexpr Shape kDefaultLoadMiddle = {32, 128, 4, true, false, false, false, 0};
 constexpr Shape kDefaultLoadSmall = {16, kDefaultThreads, 4, true, false, false, false, 0};
 constexpr int64_t kMiddleLoadBytes = int64_t(32) << 20;
+#ifndef KVIO_PACED_LOAD_BYTES
+#define KVIO_PACED_LOAD_BYTES kMiddleLoadBytes
+#endif
+constexpr int64_t kPacedLoadBytes = KVIO_PACED_LOAD_BYTES;      // a build may have small loads paced
 constexpr int64_t kSmallLoadBytes = int64_t(4) << 20;
 constexpr int64_t kSmallLoadBytesPageFirst = int64_t(512) << 10;
 constexpr Shape kDefaultOffload = {32, kDefaultThreads, 16, true, false, false, false, 0};

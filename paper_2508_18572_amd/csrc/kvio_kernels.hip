@@ -470,7 +470,7 @@ __device__ __forceinline__ void fetch_args(Args &a) {
                  "s"(a.spans[0].page_idx), "s"(a.spans[0].host_tokens), "s"(a.spans[0].num_tokens), "s"(a.spans[0].token0));
 }
 
-// What a wave of a paced offload sleeps behind a step that moved `vecs` vectors.
+// What a paced wave sleeps behind a step that moved `vecs` vectors.
 __device__ __forceinline__ void rest(Args &a, int vecs) {
     for (int i = static_cast<int>(static_cast<uint32_t>(a.pause) * static_cast<uint32_t>(vecs) >> 16); i > 0; --i) __builtin_amdgcn_s_sleep(1);
 }
@@ -581,6 +581,12 @@ __device__ __forceinline__ void copy_tiles(Args &a) {
             for (int k = 0; k < U; ++k) asm volatile("" : "+v"(at[k]));
         }
         write_tile<DIR, U, NT, SC1, WIDE, HL>(a, t, slot, lane, buf);
+        if (a.pause != 0) {
+            // In step, so that the pause leaves the compute unit's queue empty
+            // (load_pause).  Waves that have ended are not waited for.
+            __builtin_amdgcn_s_barrier();
+            rest(a, t.end);
+        }
     } while (more);
 }
 
@@ -917,6 +923,13 @@ static void launch_layout(const CopyArgs &a, dim3 grid, dim3 block, hipStream_t 
 constexpr int64_t kPacedMBps = 46500;
 constexpr int64_t kPacedSleep = 700;
 constexpr int kPacedWavesPerWg = 4;
+// Of loads: ns of an unhindered step of 4 KiB, longer where rows lie apart, and the
+// longest sleep.
+constexpr int64_t kLoadMBps = 57400;
+constexpr int64_t kLoadTrip = 2360;
+constexpr int64_t kLoadTripPageFirst = 2760;
+constexpr int64_t kLongestRest = 1000;
+constexpr int kLoadWavesPerWg = 6;
 
 static int32_t pause_of(const CopyArgs &a, int U) {
     const int64_t tile = a.whole_rows ? int64_t(a.tile_rows) * a.vec_per_row : a.tile_vecs;
@@ -926,6 +939,33 @@ static int32_t pause_of(const CopyArgs &a, int U) {
                                                           : 410 + step * 16 * (step < 64 * U ? 100 : 80) / 1024 + 480 / steps;
     const int64_t spare = a.waves * step * 16 * 1000 / kPacedMBps - takes;
     return spare <= 0 || spare > kPacedSleep ? 0 : static_cast<int32_t>((spare << 16) / 26 / step + 1);      // 26 ns: 64 cycles
+}
+
+// Loads of kPacedLoadBytes or more: the waves of a workgroup wait for one another
+// behind a step and then sleep for what the step would otherwise queue for on the
+// link, its share of the link's rate less the way of an unhindered step.  A compute
+// unit returns its vector loads in order, so while its waves keep host reads in
+// flight without a gap, every load of a kernel that shares it takes a host round
+// trip.  And reads that queue on the link slow an offload beside them.
+// A decode step of 7.3 ms beside loads (ms | the load's GB/s), a load alone, and
+// with a background offload beside (both together), 39 waves; 48 waves:
+//   neither          21.6 | 56.2   57.5    98.8;  26.6 | 56.8   57.5    94.9
+//   in step          11.9 | 56.7   57.5    97.8;  19.6 | 57.2   57.5    94.0
+//   slept, 0.4 us    17.0 | 55.2   57.3   102.3;  20.6 | 56.0   57.3    94.7
+//   as now           11.3 | 55.8   57.4   102.6;  10.5 | 56.5   57.5   102.5
+// Alone, 48 MiB of 2 KiB rows: 16 x 192 879 us without, 881 as now, 8 x 384 894, 880, 16 x 256
+// 884, 879.  Not for larger steps, whose way is longer (16 x 192 of 8 KiB 881, 929), nor
+// workgroups bound by their compute units (4 x 1024 1156, 1213).
+static int32_t load_pause(const CopyArgs &a) {
+    if (a.tile_vecs > 256 || a.waves_per_wg > kLoadWavesPerWg) return 0;
+    int64_t rows = 0;
+    for (int32_t i = 0; i < a.n_spans; ++i) rows += a.spans[i].num_tokens;
+    const int64_t plane = rows * a.vec_per_row * a.heads_per_tile;          // vectors
+    if (plane < kPacedLoadBytes / 16 / a.planes) return 0;
+    const int64_t step = std::max<int64_t>(plane / a.plane_tiles, 1);
+    const int64_t trip = a.host_layout == KVIO_HOST_PAGE_FIRST ? kLoadTripPageFirst : kLoadTrip;
+    const int64_t spare = std::min(a.waves * step * 16 * 1000 / kLoadMBps - trip, kLongestRest);
+    return spare <= 0 ? 0 : static_cast<int32_t>((spare << 16) / 26 / step + 1);
 }
 
 template <int DIR, int U, bool NT, bool SC1>
@@ -945,7 +985,7 @@ static hipError_t launch_u(CopyArgs &a, const Shape &s, hipStream_t stream) {
     a.step_vecs = a.waves * a.tile_vecs;         // used where it stays inside a span
     a.step_rows = a.step_vecs / a.vec_per_row;
     a.step_cols = a.step_vecs % a.vec_per_row;
-    a.pause = DIR == kOffload && !SC1 && !s.local && !a.transpose ? pause_of(a, U) : 0;
+    a.pause = s.local || a.transpose ? 0 : DIR == kLoad ? load_pause(a) : SC1 ? 0 : pause_of(a, U);
     switch (a.host_layout) {
         case kHostPageFirst: launch_layout<DIR, U, NT, SC1, kHostPageFirst>(a, grid, block, stream); break;
         case kHostHeadMajor: launch_layout<DIR, U, NT, SC1, kHostHeadMajor>(a, grid, block, stream); break;

@@ -107,6 +107,7 @@ inline void __builtin_amdgcn_wave_barrier() { emu_ballot(true, "wave_barrier"); 
 inline bool __any(bool v) { return emu_ballot(v, "any") != 0; }
 inline bool __all(bool v) { return emu_ballot(v, "all") == ~uint64_t(0); }
 inline void __builtin_amdgcn_s_sleep(int) {}
+inline void __builtin_amdgcn_s_barrier() {}      // waves run one after another and share nothing
 inline void *__builtin_amdgcn_kernarg_segment_ptr() { return emu_kernarg(); }
 template <class T>
 T atomicCAS(T *p, T cmp, T val) { T old = *p; if (old == cmp) *p = val; return old; }

@@ -288,14 +288,13 @@ def run_full_steps(out):
 
 def run_default_loads(out):
     """Default loads below 32 MiB keep 256 KiB in flight (two of them on two streams
-    fill the link together), larger ones at most 156 (more slows an offload beside
-    them), and rows too narrow to fill a step take as many waves more."""
+    fill the link together), larger ones 192, and rows too narrow to fill a step take as many waves more."""
     kv = load(out)
     for layout in range(3):
         for shift in range(15, 25):
             assert kv._lib.emu_default_load_kib(1 << shift, layout) == 256, (layout, shift)
         for shift in range(25, 36):
-            assert 128 < kv._lib.emu_default_load_kib(1 << shift, layout) <= 156, (layout, shift)
+            assert kv._lib.emu_default_load_kib(1 << shift, layout) == 192, (layout, shift)
     L, P = 1, 16
     for R, T, waves in ((16, 16384, 256), (32, 8192, 128), (48, 8192, 85), (512, 512, 64)):
         keep = [[Memory(kv, T * R, 1, 1) for _ in range(L)] for _ in range(2)]
@@ -355,6 +354,40 @@ def run_pauses(out):
     assert pause(0, 16, 1, (8, 256, 4)) == pause(0, 2064, 1, (16, 64, 4)) == 0
 
 
+def run_load_pauses(out):
+    """Loads of a size (64 KiB in this build, 32 MiB otherwise) whose waves would queue on
+    the link sleep behind each step, longer the more they would; none where they do
+    not fill the link, with larger steps, with large workgroups and from device memory."""
+    kv = load(out)
+
+    def pause(layout, quota, T=2048, local=0, P=16, H=2, De=256):
+        R = H * De
+        keep = [Memory(kv, T * R, 1, 1) for _ in range(2)]
+        h = kv.kvio_pool_create(1, H, De, 1, P, T, [keep[0].ptr], [keep[1].ptr], kv.launch(*quota), None, layout)
+        src, table = Memory(kv, 2 * T * R, local, 1), Memory(kv, T // P * 4, 1, 1)
+        src.array[:] = np.random.default_rng(T).integers(0, 256, len(src.array), dtype=np.uint8)
+        pages = np.random.default_rng(R).permutation(T // P).astype(np.int32)
+        table.array[:] = pages.view(np.uint8)
+        kv.kvio_load(h, [(src.ptr, T, T, table.ptr)], 0, 1)
+        img = np.zeros((2, 1, T, R), np.uint8)
+        oracle.load_layout(img[0], img[1], P, [(src.array, T, T, pages)], LAYOUT[layout], num_heads=H)
+        assert np.array_equal(np.stack([m.array.reshape(1, T, R) for m in keep]), img)
+        got = kv._lib.emu_last_pause()
+        kv.kvio_pool_destroy(h)
+        for m in keep + [src, table]:
+            m.free()
+        return got
+
+    for layout in range(3):
+        at = {q: pause(layout, q) for q in ((8, 256, 4), (13, 192, 4), (7, 384, 4), (16, 192, 4), (16, 256, 4), (16, 192, 8), (16, 256, 16))}
+        assert at[8, 256, 4] == at[16, 192, 8] == at[16, 256, 16] == 0, at
+        assert at[13, 192, 4] <= at[7, 384, 4] < at[16, 192, 4] <= at[16, 256, 4] <= 40, at
+        assert 20 <= at[16, 192, 4] and (8 <= at[13, 192, 4] <= 20 or layout == 1), at
+        assert pause(layout, (16, 192, 4), local=1) == 0
+        assert pause(layout, (16, 192, 4), T=48) == 0                # below the size
+    assert pause(0, (4, 1024, 4)) == pause(0, (6, 512, 4)) == 0
+
+
 def run_short_contexts(out):
     """Short head-major contexts on a fixed quota: a wave's step holds the rows of all
     heads (or of as many as fit), not one head's few vectors; long contexts, the
@@ -411,7 +444,7 @@ def run_short_contexts(out):
 def emulated(tmp_path_factory):
     out = {}
     for name, extra in (("whole", ()), ("split", ("-DKVIO_MAX_SPAN_VECS=40",)),
-                        ("planes", ("-DKVIO_MAX_PLANES=4",))):
+                        ("planes", ("-DKVIO_MAX_PLANES=4", "-DKVIO_PACED_LOAD_BYTES=65536"))):
         out[name] = str(tmp_path_factory.mktemp(name))
         build(out[name], extra)
     return out
@@ -437,7 +470,7 @@ def test_noalloc_table_in_the_arguments(emulated, name):
 
 
 @pytest.mark.parametrize("name,run", [("planes", "run_staged_layers"), ("whole", "run_full_steps"),
-                                      ("whole", "run_default_loads"), ("whole", "run_pauses"),
+                                      ("whole", "run_default_loads"), ("whole", "run_pauses"), ("planes", "run_load_pauses"),
                                       ("whole", "run_short_contexts")])
 def test_launch_limits_and_steps(emulated, name, run):
     code = (f"import sys; sys.path[:0] = [{ROOT!r}, {os.path.join(ROOT, 'tests')!r}]\n"
