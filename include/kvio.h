@@ -103,7 +103,7 @@ typedef enum kvio_status {
 
 /* Launch shaping (Sec. 4.2: a small number of large workgroups keeps the I/O
  * kernel on few compute units; cache bypass limits pollution).  Zero fields
- * take the library defaults: loads 13 workgroups of three waves, below 32 MiB 16
+ * take the library defaults: loads 16 workgroups of three waves, below 32 MiB
  * of four or 32 of two, offloads 32 or 64 of four.  Two defaults take more of the GPU, and
  * workgroups != 0 turns both off.  Where every chunk of a call lies in the
  * memory of the pool's own GPU (handles only), nothing crosses the host link and the call takes 1024
@@ -112,10 +112,13 @@ typedef enum kvio_status {
  * An offload whose waves x step come to about 64 to 128 KiB (16 workgroups of one
  * wave with 4 KiB steps) is a background quota: it moves 46.5 GB/s at most, the
  * rate that leaves a load beside it most of the link.
+ * A load of 32 MiB or more with 4 KiB steps and at most 6 waves a workgroup sleeps
+ * between steps where its reads would otherwise queue on the link.
  * Results never depend on these. */
 #define KVIO_LAUNCH_CACHED 0x1     /* plain loads/stores instead of non-temporal ones */
-#define KVIO_LAUNCH_NO_LDS 0x2     /* head-major chunks of segments below 64 bytes: by address, not through LDS
-                                      (the others never use LDS) */
+#define KVIO_LAUNCH_NO_LDS 0x2     /* head-major chunks always by address: also segments below 64 bytes, and
+                                      contexts of a few tokens on a grid of the caller's, which otherwise go
+                                      through LDS (the other layouts never use it) */
 /* KVIO_LAUNCH_STAGED (token-major and head-major chunks): instead of
  * wavefronts reading (writing) the pinned chunk across the host link, the
  * copy engine moves the chunk's contiguous runs to (from) an HBM staging buffer
